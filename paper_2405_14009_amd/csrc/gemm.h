@@ -52,18 +52,30 @@ struct GemmParams {
   // bias gradient of a linear layer is exactly this sum of its output
   // gradient, the B operand of its weight-gradient product.  The workgroup of
   // tile-row tm sums the B tiles it stages anyway whose k-tile index t has
-  // t mod tiles_m == tm, into row tm of colsum_work (gemm_colsum_floats
-  // floats); a second kernel adds the rows in a fixed order and writes
-  // (colsum_acc: adds) them to colsum_out[0, N) in fp32.  nullptr: off.
+  // t mod tiles_m == tm, into row tm of colsum_work (GemmWork::colsum_floats
+  // floats; split s of a split reduction into row s * tiles_m + tm); a second
+  // kernel adds the rows in a fixed order and writes (colsum_acc: adds) them to
+  // colsum_out[0, N) in fp32.  nullptr: off.
   float* colsum_out;
   int colsum_acc;
   float* colsum_work;
+  long colsum_floats;
+  // Split reductions: with splits > 1 (set by the launchers, which also point
+  // C at the partials) workgroup row blockIdx.y multiplies k in
+  // [y * split_k, (y + 1) * split_k) and stores its fp32 partial of the whole
+  // [M, N] output at C + y * M * N; splitk_finish then adds the partials in
+  // order and runs the epilogue.  The launchers split where it pays and
+  // split_floats of workspace at split_work (nullptr: none) allow it.
+  float* split_work;
+  long split_floats;
+  int splits, split_k;
   // Reduction split into segments of kseg_len (0: one segment).  Segment s
   // of A / B starts at segA[s] / segB[s] (A, B are ignored); within a segment
   // the layouts above apply with k counted from the segment start.  Used to
   // run several micro-batches' weight gradients as one product over their
   // concatenated tokens.
   int kseg_len;
+  int kseg_pad;  // set by the bf16 launcher: kseg_len rounded up to whole k-tiles, K counts padded segments
   const void* segA[GEMM_MAX_SEG];
   const void* segB[GEMM_MAX_SEG];
 };
@@ -71,35 +83,15 @@ struct GemmParams {
 // Shapes must satisfy: M, N, K multiples of 8 when an operand is loaded
 // along that dimension in 8-element vectors (checked by the caller).
 hipError_t gemm_bf16(const GemmParams& p, hipStream_t s);
-// Floats of colsum_work a bf16 GEMM of M rows and N columns needs (its
-// tile-rows are 256 high).
-inline long gemm_colsum_floats(long M, long N) { return ((M + 255) / 256) * N; }
+// Workspace of a product of [M, N] over nseg segments of seg each: floats of
+// split_work that it can make use of, and of colsum_work that column sums need.
+struct GemmWork {
+  long split_floats, colsum_floats;
+};
+GemmWork gemm_bf16_work(long M, long N, long nseg, long seg);
+GemmWork gemm_f32_work(long M, long N, long nseg, long seg);
+constexpr long GEMM_SPLIT_MAX_FLOATS = 16L << 20;  // most partials of one product
 hipError_t gemm_f32(const GemmParams& p, hipStream_t s);
-
-template <int EPI, class E>
-__device__ __forceinline__ void epi_store(const GemmParams& p, E* C, int m, int n, float v) {
-  const long i = (long)m * p.ldc + n;
-  if constexpr (EPI == EPI_STORE) {
-    C[i] = from_f32<E>(v);
-  } else if constexpr (EPI == EPI_BIAS) {
-    C[i] = from_f32<E>(v + p.bias[n]);
-  } else if constexpr (EPI == EPI_BIAS_RESID) {
-    const E* r = (const E*)p.resid;
-    C[i] = from_f32<E>(v + p.bias[n] + to_f32(r[(long)m * p.ld_resid + n]));
-  } else if constexpr (EPI == EPI_BIAS_GELU) {
-    const float u = v + p.bias[n], sg = gelu_sig(u);
-    C[i] = from_f32<E>(gelu_grad_s(u, sg));
-    ((E*)p.C2)[(long)m * p.ldc2 + n] = from_f32<E>(u * sg);
-  } else if constexpr (EPI == EPI_GELU_BWD) {
-    const E* d = (const E*)p.aux;
-    C[i] = from_f32<E>(v * to_f32(d[(long)m * p.ld_aux + n]));
-  } else if constexpr (EPI == EPI_F32_ACC) {
-    float* c = (float*)C;
-    c[i] = p.accumulate ? c[i] + v : v;
-  } else {  // EPI_F32_STORE
-    ((float*)C)[i] = v;
-  }
-}
 
 // Per-element input of an epilogue at (m, n..n+3): the residual, GeLU's
 // input, or the fp32 gradient being accumulated into.  Fetched separately
@@ -198,3 +190,7 @@ template <int EPI, class E>
 struct EpiOut { typedef E type; };
 template <class E> struct EpiOut<EPI_F32_ACC, E> { typedef float type; };
 template <class E> struct EpiOut<EPI_F32_STORE, E> { typedef float type; };
+
+// Adds the partials of a split reduction in order and runs the epilogue of p
+// (whose C is the output again).
+hipError_t splitk_finish(int elt, const GemmParams& p, hipStream_t s);

@@ -62,8 +62,14 @@ __device__ __forceinline__ int swz_k(int r) {
   static_assert(BK == 64, "k-tiles of 64");
   return (r & 7) ^ ((r >> 3) & 3);
 }
-// m/n-contiguous tiles: chunk c of k-row r lives at chunk c ^ swz_mn(r).
-__device__ __forceinline__ int swz_mn(int r) { return (r & 3) << 2; }
+// m/n-contiguous tiles: chunk c of k-row r lives at chunk c ^ swz_mn(r): the
+// four k-rows of a transposing read (4 chunks each) on distinct banks.  (64-wide
+// tiles: two k-rows fill the 256 bytes of the banks, so only the second pair moves.)
+template <int ROWS>
+__device__ __forceinline__ int swz_mn(int r) {
+  static_assert(ROWS >= 128 || ROWS == 64, "tile widths");
+  return ROWS == 64 ? (r & 2) << 1 : (r & 3) << 2;
+}
 
 // One operand's share of the per-k-tile copy: this wave issues instructions
 // g = wave + NW q (q < NI) of the operand's 1 KB slices (NW waves).  Every slice of a wave
@@ -85,7 +91,7 @@ struct Copier {
       base = (uint32_t)((long)mn * ld * 2);
     } else {
       const int krow = RPI * wave + lane / CPR;
-      const int c = (lane % CPR) ^ swz_mn(krow);
+      const int c = (lane % CPR) ^ swz_mn<ROWS>(krow);
       kk = krow;
       mn = mn0 + 8 * c;
       base = (uint32_t)(2 * mn);
@@ -111,14 +117,14 @@ struct Copier {
 
 // Column sums over k of the staged m/n-contiguous B tiles ([BK][BN] bf16,
 // 16-byte chunks swizzled by k-row), accumulated over the k-tiles a
-// workgroup takes part for: thread t (of 512) owns chunk column t % (BN / 8)
+// workgroup takes part for: thread t (of NTH) owns chunk column t % (BN / 8)
 // and k-rows t / (BN / 8) + R i of every tile (R row groups), 8 fp32 partial
 // sums.  finish() adds the R partials of each column in a fixed order through
 // LDS and stores the workgroup's row of partial sums, so the result is
 // reproducible.
-template <int BN, int BK>
+template <int BN, int BK, int NTH = 512>
 struct ColSums {
-  static constexpr int CC = BN / 8, R = 512 / CC, RPT = BK / R;
+  static constexpr int CC = BN / 8, R = NTH / CC, RPT = BK / R;
   static_assert(BK % R == 0, "row groups");
   static constexpr int RED_BYTES = R * BN * 4;
   float s[8];
@@ -133,7 +139,7 @@ struct ColSums {
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       const int k = rg + R * i;
-      const uint4 v = *(const uint4*)(tb + k * (BN * 2) + ((cc ^ swz_mn(k)) << 4));
+      const uint4 v = *(const uint4*)(tb + k * (BN * 2) + ((cc ^ swz_mn<BN>(k)) << 4));
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -143,7 +149,7 @@ struct ColSums {
     }
   }
   // red: RED_BYTES of LDS that no wave touches meanwhile; every wave calls it.
-  __device__ __forceinline__ void finish(float* red, const GemmParams& p, int tm, int n0, int tid) {
+  __device__ __forceinline__ void finish(float* red, const GemmParams& p, int row, int n0, int tid) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[rg * BN + 8 * cc + e] = s[e];
     __syncthreads();
@@ -152,7 +158,7 @@ struct ColSums {
 #pragma unroll 8
       for (int r = 0; r < R; ++r) t += red[r * BN + tid];
       const int n = n0 + tid;
-      if (n < p.N) p.colsum_work[(long)tm * p.N + n] = t;
+      if (n < p.N) p.colsum_work[(long)row * p.N + n] = t;
     }
     __syncthreads();
   }
@@ -181,7 +187,7 @@ struct FragOffsets {
 #pragma unroll
       for (int b = 0; b < NBLK; ++b) {
         const int mn = r0 + 32 * b + 16 * ((lane >> 4) & 1) + 4 * (i & 3);
-        off[b] = (uint32_t)(k * (ROWS * 2) + (((mn >> 3) ^ swz_mn(k)) << 4) + 8 * (i & 1));
+        off[b] = (uint32_t)(k * (ROWS * 2) + (((mn >> 3) ^ swz_mn<ROWS>(k)) << 4) + 8 * (i & 1));
       }
     }
   }
@@ -203,7 +209,7 @@ __device__ __forceinline__ bf16x8 frag(const char* tile, const FragOffsets<ROWS,
   }
 }
 
-// MFMAs of one staged k-tile for a wave tile of 4 x TN blocks of 32x32 over
+// MFMAs of one staged k-tile for a wave tile of TM x TN blocks of 32x32 over
 // NKS k-steps.  The fragments of k-step ks+1 are read while the MFMAs of
 // k-step ks issue; scheduling groups pin that interleave (one MFMA, then that
 // k-step's share of LDS reads) so the reads stay ahead of their use.
@@ -214,37 +220,37 @@ __device__ __forceinline__ bf16x8 frag(const char* tile, const FragOffsets<ROWS,
 // matrix core has work while those reads are in flight after the k-tile
 // barrier; mma_flush adds the last pending product.  (Zero fragments make the
 // first call's pending MFMAs a no-op.)
-template <int TN>
-__device__ __forceinline__ void mma_flush(f32x16 (&acc)[4][TN], const bf16x8 (&pa)[4], const bf16x8 (&pb)[TN]) {
+template <int TM, int TN>
+__device__ __forceinline__ void mma_flush(f32x16 (&acc)[TM][TN], const bf16x8 (&pa)[TM], const bf16x8 (&pb)[TN]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[i], pb[j], acc[i][j], 0, 0, 0);
 }
-template <int TN>
-__device__ __forceinline__ void mma_pending_clear(bf16x8 (&pa)[4], bf16x8 (&pb)[TN]) {
+template <int TM, int TN>
+__device__ __forceinline__ void mma_pending_clear(bf16x8 (&pa)[TM], bf16x8 (&pb)[TN]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) pa[i] = bf16x8{};
+  for (int i = 0; i < TM; ++i) pa[i] = bf16x8{};
 #pragma unroll
   for (int j = 0; j < TN; ++j) pb[j] = bf16x8{};
 }
-template <int BM, int BN, bool AK, bool BKC, int TN, int NKS, int BK, bool DEFER, typename Step>
-__device__ __forceinline__ void mma_tile(f32x16 (&acc)[4][TN], const char* ta, const char* tb,
-                                         const FragOffsets<BM, AK, 4, NKS, BK>& fa,
+template <int BM, int BN, bool AK, bool BKC, int TM, int TN, int NKS, int BK, bool DEFER, typename Step>
+__device__ __forceinline__ void mma_tile(f32x16 (&acc)[TM][TN], const char* ta, const char* tb,
+                                         const FragOffsets<BM, AK, TM, NKS, BK>& fa,
                                          const FragOffsets<BN, BKC, TN, NKS, BK>& fb, Step step,
-                                         bf16x8 (&pa)[4], bf16x8 (&pb)[TN]) {
-  constexpr int READS = 4 * (AK ? 1 : 2) + TN * (BKC ? 1 : 2);  // LDS read instructions per k-step
-  constexpr int NMFMA = 4 * TN;
+                                         bf16x8 (&pa)[TM], bf16x8 (&pb)[TN]) {
+  constexpr int READS = TM * (AK ? 1 : 2) + TN * (BKC ? 1 : 2);  // LDS read instructions per k-step
+  constexpr int NMFMA = TM * TN;
   constexpr int PER = (READS + NMFMA - 1) / NMFMA;
-  bf16x8 af[2][4], bfr[2][TN];
+  bf16x8 af[2][TM], bfr[2][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) af[0][i] = frag(ta, fa, i, 0);
+  for (int i = 0; i < TM; ++i) af[0][i] = frag(ta, fa, i, 0);
 #pragma unroll
   for (int j = 0; j < TN; ++j) bfr[0][j] = frag(tb, fb, j, 0);
   __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
   if constexpr (DEFER) {
-    mma_flush<TN>(acc, pa, pb);
+    mma_flush<TM, TN>(acc, pa, pb);
     __builtin_amdgcn_sched_group_barrier(0x008, NMFMA, 0);
   }
 #pragma unroll
@@ -255,19 +261,19 @@ __device__ __forceinline__ void mma_tile(f32x16 (&acc)[4][TN], const char* ta, c
     __builtin_amdgcn_sched_barrier(0);
     if (ks + 1 < NKS) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) af[c ^ 1][i] = frag(ta, fa, i, ks + 1);
+      for (int i = 0; i < TM; ++i) af[c ^ 1][i] = frag(ta, fa, i, ks + 1);
 #pragma unroll
       for (int j = 0; j < TN; ++j) bfr[c ^ 1][j] = frag(tb, fb, j, ks + 1);
     }
     if (DEFER && ks + 1 == NKS) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pa[i] = af[c][i];
+      for (int i = 0; i < TM; ++i) pa[i] = af[c][i];
 #pragma unroll
       for (int j = 0; j < TN; ++j) pb[j] = bfr[c][j];
       break;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
@@ -294,8 +300,8 @@ __device__ __forceinline__ void mma_tile(f32x16 (&acc)[4][TN], const char* ta, c
 // finished, so those loads overlap instead of each costing a round trip
 // (LOOK; without it each block-row's inputs are fetched as it is finished,
 // which needs 32 fewer registers).
-template <int EPI, int TN, int I0, int I1, bool LOOK = true>
-__device__ __forceinline__ void epilogue(const GemmParams& p, f32x16 (&acc)[4][TN], float* sm, int m0,
+template <int EPI, int TN, int I0, int I1, bool LOOK = true, int TM = 4>
+__device__ __forceinline__ void epilogue(const GemmParams& p, f32x16 (&acc)[TM][TN], float* sm, int m0,
                                          int n0, int lane, long c_off) {
   constexpr int COLS = 32 * TN, STRIDE = COLS + 8;
   constexpr int NQ = COLS / 8;  // 4-column groups per lane per block-row
@@ -418,17 +424,23 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   const int m0 = tm * BM, n0 = tn * BN;
   if (p.causal_skip && n0 > m0 + BM - 1) return;
 
-  const int z = blockIdx.y;
+  // blockIdx.y: the product of a batch, or the split of a split reduction
+  const int split = p.splits > 1 ? blockIdx.y : 0;
+  const int z = p.splits > 1 ? 0 : blockIdx.y;
   const int zb = z / p.heads, zh = z % p.heads;
   const bf16* A = (const bf16*)p.A + zb * p.a_bs + zh * p.a_hs;
   const bf16* B = (const bf16*)p.B + zb * p.b_bs + zh * p.b_hs;
-  const long c_off = zb * p.c_bs + zh * p.c_hs;
+  const long c_off = p.splits > 1 ? (long)split * p.M * p.N : zb * p.c_bs + zh * p.c_hs;
   const i32x4 ra = make_rsrc(A, 2L * (AK ? (long)p.M * p.lda : (long)p.K * p.lda));
   const i32x4 rb = make_rsrc(B, 2L * (BKC ? (long)p.N * p.ldb : (long)p.K * p.ldb));
 
   int kb = 0, ke = p.K;
   if (p.krange == KR_BELOW) ke = min(p.K, m0 + BM);
   else if (p.krange == KR_ABOVE) kb = (m0 / BK) * BK;
+  if (p.splits > 1) {
+    kb = split * p.split_k;
+    ke = min(p.K, kb + p.split_k);
+  }
   const int nk = ke > kb ? (ke - kb + BK - 1) / BK : 0;
 
   Copier<BM, AK, NIA, NW, BK> ca;
@@ -465,8 +477,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   auto source = [&](int k0) {
     Src r{ra, rb, k0, ke};
     if (p.kseg_len > 0) {
-      const int sg = k0 / p.kseg_len;
-      r.k = k0 - sg * p.kseg_len;
+      const int sg = k0 / p.kseg_pad;
+      r.k = k0 - sg * p.kseg_pad;
       r.kend = p.kseg_len;
       r.a = make_rsrc((const bf16*)p.segA[sg] + zb * p.a_bs + zh * p.a_hs,
                       2L * (AK ? (long)p.M * p.lda : (long)p.kseg_len * p.lda));
@@ -492,7 +504,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   static_assert(NKS >= 2, "the refill spans two k-steps");
   constexpr bool DEFER = !AK && !BKC;
   bf16x8 pa[4], pb[TN];
-  mma_pending_clear<TN>(pa, pb);
+  mma_pending_clear<4, TN>(pa, pb);
 #pragma unroll
   for (int i = 0; i < NST - 1; ++i)
     if (i < nk) issue(lds + i * STAGE, kb + i * BK);
@@ -507,7 +519,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
     const Src nx = source(refill ? kb + (t + NST - 1) * BK : kb);
     char* dst = lds + si * STAGE;
     const char* st = lds + sc * STAGE;
-    mma_tile<BM, BN, AK, BKC, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
+    mma_tile<BM, BN, AK, BKC, 4, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
       if (refill && ks == 0) ca.issue(nx.a, dst, wave, p.lda, p.M, nx.k, nx.kend);
       if (refill && ks == 1) cb.issue(nx.b, dst + A_BYTES, wave, p.ldb, p.N, nx.k, nx.kend);
     }, pa, pb);
@@ -523,13 +535,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
     si = si + 1 == NST ? 0 : si + 1;
   }
 
-  if constexpr (DEFER) mma_flush<TN>(acc, pa, pb);
+  if constexpr (DEFER) mma_flush<4, TN>(acc, pa, pb);
   // LDS is free once every wave is past its last k-tile.
   __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
   static_assert(ColSums<BN, BK>::RED_BYTES <= LDS_BYTES, "column-sum reduction fits LDS");
   if constexpr (CS) {
-    if (cs_on) cs.finish((float*)lds, p, tm, n0, threadIdx.x);
+    if (cs_on) cs.finish((float*)lds, p, split * tiles_m + tm, n0, threadIdx.x);
   }
   float* sm = (float*)(lds + wave * EPI_BYTES);
   epilogue<EPI, TN, 0, 4>(p, acc, sm, m0 + wm * 128, n0 + wn * (BN / WN_), lane, c_off);
@@ -595,8 +607,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
   auto source = [&](int k0) {
     Src r{ra, rb, k0, p.K};
     if (p.kseg_len > 0) {
-      const int sg = k0 / p.kseg_len;
-      r.k = k0 - sg * p.kseg_len;
+      const int sg = k0 / p.kseg_pad;
+      r.k = k0 - sg * p.kseg_pad;
       r.kend = p.kseg_len;
       r.a = make_rsrc(p.segA[sg], 2L * (AK ? (long)p.M * p.lda : (long)p.kseg_len * p.lda));
       r.b = make_rsrc(p.segB[sg], 2L * (BKC ? (long)p.N * p.ldb : (long)p.kseg_len * p.ldb));
@@ -631,7 +643,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
     if (cs_on) cs.init(threadIdx.x);
     int sc = 0, si = 1;
     bf16x8 pa[4], pb[TN];  // the deferred last k-step of each k-tile (mma_tile)
-    mma_pending_clear<TN>(pa, pb);
+    mma_pending_clear<4, TN>(pa, pb);
     for (int t = 0; t < nk; ++t) {
       __builtin_amdgcn_sched_barrier(0);
       wait_vmcnt<0>();
@@ -642,7 +654,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
       const Src nx = source(refill ? (t + 1) * BK : 0);
       char* dst = lds + si * STAGE;
       const char* st = lds + sc * STAGE;
-      mma_tile<BM, BN, AK, BKC, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
+      mma_tile<BM, BN, AK, BKC, 4, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
         if (refill && ks == 0) ca.issue(nx.a, dst, wave, p.lda, p.M, nx.k, nx.kend);
         if (refill && ks == 1) cb.issue(nx.b, dst + A_BYTES, wave, p.ldb, p.N, nx.k, nx.kend);
       }, pa, pb);
@@ -656,7 +668,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
       sc ^= 1;
       si ^= 1;
     }
-    if constexpr (DEFER) mma_flush<TN>(acc, pa, pb);
+    if constexpr (DEFER) mma_flush<4, TN>(acc, pa, pb);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();  // every wave is past the last k-tile: both stages are free
     const int cm0 = m0, cn0 = n0, ctm = tm;
@@ -799,17 +811,23 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
   const int m0 = tm * BM, n0 = tn * BN;
   if (p.causal_skip && n0 > m0 + BM - 1) return;
 
-  const int z = blockIdx.y;
+  // blockIdx.y: the product of a batch, or the split of a split reduction
+  const int split = p.splits > 1 ? blockIdx.y : 0;
+  const int z = p.splits > 1 ? 0 : blockIdx.y;
   const int zb = z / p.heads, zh = z % p.heads;
   const bf16* A = (const bf16*)p.A + zb * p.a_bs + zh * p.a_hs;
   const bf16* B = (const bf16*)p.B + zb * p.b_bs + zh * p.b_hs;
-  const long c_off = zb * p.c_bs + zh * p.c_hs;
+  const long c_off = p.splits > 1 ? (long)split * p.M * p.N : zb * p.c_bs + zh * p.c_hs;
   const i32x4 ra = make_rsrc(A, 2L * (AK ? (long)p.M * p.lda : (long)p.K * p.lda));
   const i32x4 rb = make_rsrc(B, 2L * (BKC ? (long)p.N * p.ldb : (long)p.K * p.ldb));
 
   int kb = 0, ke = p.K;
   if (p.krange == KR_BELOW) ke = min(p.K, m0 + BM);
   else if (p.krange == KR_ABOVE) kb = (m0 / BK) * BK;
+  if (p.splits > 1) {
+    kb = split * p.split_k;
+    ke = min(p.K, kb + p.split_k);
+  }
   const int nk = ke > kb ? (ke - kb + BK - 1) / BK : 0;
 
   Copier<BM, AK, NIA, NW, BK> ca;
@@ -844,8 +862,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
   auto source = [&](int k0) {
     Src r{ra, rb, k0, ke};
     if (p.kseg_len > 0) {
-      const int sg = k0 / p.kseg_len;
-      r.k = k0 - sg * p.kseg_len;
+      const int sg = k0 / p.kseg_pad;
+      r.k = k0 - sg * p.kseg_pad;
       r.kend = p.kseg_len;
       r.a = make_rsrc((const bf16*)p.segA[sg] + zb * p.a_bs + zh * p.a_hs,
                       2L * (AK ? (long)p.M * p.lda : (long)p.kseg_len * p.lda));
@@ -921,7 +939,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
   __syncthreads();
   static_assert(ColSums<BN, BK>::RED_BYTES <= LDS_BYTES, "column-sum reduction fits LDS");
   if constexpr (CS) {
-    if (cs_on) cs.finish((float*)lds, p, tm, n0, threadIdx.x);
+    if (cs_on) cs.finish((float*)lds, p, split * tiles_m + tm, n0, threadIdx.x);
   }
   // The partner's slot is read only by this wave, so after the reduction it
   // serves as this wave's epilogue tile.  (The gradient-accumulating
@@ -938,68 +956,6 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
     ksplit_reduce<TN, 1>(acc, mine, theirs, lane);
     epilogue<EPI, TN, 2, 4, LOOK>(p, acc, theirs, m0 + wm * 128, n0 + wn * (BN / WN_), lane, c_off);
   }
-}
-
-template <int BN, int KS, int NST, int GM, bool AK, bool BKC, int EPI>
-hipError_t launch_bf16_pp(const GemmParams& p, hipStream_t s) {
-  const long z = (long)p.batch * p.heads;
-  const int tiles = ((p.M + 255) / 256) * ((p.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_bf16_pp_kernel<BN, KS, NST, GM, AK, BKC, EPI>), dim3(tiles, z), dim3(512), 0, s,
-                     p);
-  return hipGetLastError();
-}
-
-// Launch of one kernel variant over the whole (tiles, batch x heads) grid.
-template <int BM, int BN, int NW, int KS, int BK, int NST, bool AK, bool BKC, int EPI>
-hipError_t launch_bf16_variant(const GemmParams& p, hipStream_t s) {
-  const long z = (long)p.batch * p.heads;
-  const int tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, NW, KS, BK, NST, AK, BKC, EPI>), dim3(tiles, z),
-                     dim3(64 * NW), 0, s, p);
-  return hipGetLastError();
-}
-
-template <bool AK, bool BKC, int EPI>
-hipError_t launch_bf16_persist(const GemmParams& p, hipStream_t s) {
-  const int ntiles = ((p.M + 255) / 256) * ((p.N + 255) / 256);
-  const int per_xcd = std::max(1, device_compute_units() / 8);
-  const int nq = std::min(ntiles / 8, per_xcd);
-  // Deferred last k-steps (mma_tile) pay off on the long reductions of
-  // batched weight gradients (-2 % batched, -7 % for one-round launches), not
-  // on single micro-batch ones (+2.4 % at K = 2048).
-  if (p.K >= 8192)
-    hipLaunchKernelGGL((gemm_bf16_persist_kernel<EPI, AK, BKC, true>), dim3(8 * nq), dim3(512), 0, s, p);
-  else
-    hipLaunchKernelGGL((gemm_bf16_persist_kernel<EPI, AK, BKC, false>), dim3(8 * nq), dim3(512), 0, s, p);
-  return hipGetLastError();
-}
-
-template <bool AK, bool BKC, int EPI>
-hipError_t launch_bf16(const GemmParams& p, hipStream_t s) {
-  const long z = (long)p.batch * p.heads;
-  auto cost = [&](int bm, int bn) {
-    long t = (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn) * z;
-    return ((t + 255) / 256) * (long)bm * bn;
-  };
-  // Tile choice: the fewest (waves of 256 workgroups) x (tile area), i.e. the
-  // least padded work on 256 compute units; ties go to the larger tile, which
-  // re-reads its operands less.
-  // 256 x 128 tiles run the ping-pong k-split kernel (three stages, tile-rows
-  // grouped by four); 256 x 256 tiles the plain two-stage kernel, which
-  // measured as fast as its ping-pong form.
-  if (p.N <= 128 || cost(256, 128) < cost(256, 256))
-    return launch_bf16_pp<128, 2, 3, 4, AK, BKC, EPI>(p, s);
-  // Weight-gradient products of more than one round of tiles run the
-  // persistent kernel: each workgroup's next tile starts copying while the
-  // previous tile's fp32 gradient update runs (measured on the 6.7B stage's
-  // single-micro-batch products: 3-4 % faster; neutral for the forward and
-  // input-gradient products, which keep one tile per workgroup).
-  if constexpr (!AK && !BKC) {
-    const long ntiles = (long)((p.M + 255) / 256) * ((p.N + 255) / 256);
-    if (z == 1 && p.krange == KR_FULL && !p.causal_skip && ntiles % 8 == 0 && ntiles > device_compute_units())
-      return launch_bf16_persist<AK, BKC, EPI>(p, s);
-  }
-  return launch_bf16_variant<256, 256, 8, 1, 64, 2, AK, BKC, EPI>(p, s);
 }
 
 }  // namespace

@@ -1,6 +1,6 @@
 // bf16 GEMMs with A k-contiguous and B n-contiguous (forward Y = X W, and
 // the attention products P V and dS K), plus the top-level bf16 dispatcher.
-#include "gemm_bf16_kernel.h"
+#include "gemm_bf16_tile.h"
 
 hipError_t gemm_bf16_nt(const GemmParams& p, hipStream_t s);
 hipError_t gemm_bf16_tn(const GemmParams& p, hipStream_t s);
@@ -17,9 +17,7 @@ static hipError_t gemm_bf16_nn(const GemmParams& p, hipStream_t s) {
 
 hipError_t gemm_bf16(const GemmParams& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0 || p.batch * p.heads <= 0) return hipSuccess;
-  // a segmented reduction needs whole 64-deep k-tiles per segment
-  if (p.kseg_len > 0 && (p.kseg_len % 64 || p.K % p.kseg_len || p.K / p.kseg_len > GEMM_MAX_SEG ||
-                         p.krange != KR_FULL))
+  if (p.kseg_len > 0 && (p.K % p.kseg_len || p.K / p.kseg_len > GEMM_MAX_SEG || p.krange != KR_FULL))
     return hipErrorInvalidValue;
   if (p.a_kcontig && !p.b_kcontig) return gemm_bf16_nn(p, s);
   // column sums of B: weight-gradient layout only, with its workspace
@@ -28,4 +26,12 @@ hipError_t gemm_bf16(const GemmParams& p, hipStream_t s) {
   if (p.a_kcontig && p.b_kcontig) return gemm_bf16_nt(p, s);
   if (!p.a_kcontig && !p.b_kcontig) return gemm_bf16_tn(p, s);
   return hipErrorInvalidValue;
+}
+
+GemmWork gemm_bf16_work(long M, long N, long nseg, long seg) {
+  // sized for 256 compute units; on a device with others the launcher splits
+  // within that room
+  const GemmPlan pl =
+      plan_bf16(M, N, nseg * ((seg + 63) / 64) * 64, 1, GEMM_SPLIT_MAX_FLOATS, -1, 256);
+  return {pl.split_floats, std::max(pl.colsum_rows(M), (M + 255) / 256) * N};
 }

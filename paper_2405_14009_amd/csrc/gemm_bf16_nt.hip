@@ -1,6 +1,6 @@
 // bf16 GEMMs with both operands k-contiguous: the input-gradient products
 // dX = dY W^T and the attention scores Q K^T / dO V^T.
-#include "gemm_bf16_kernel.h"
+#include "gemm_bf16_tile.h"
 
 hipError_t gemm_bf16_nt(const GemmParams& p, hipStream_t s) {
   switch (p.epi) {

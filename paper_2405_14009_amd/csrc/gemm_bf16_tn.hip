@@ -1,7 +1,7 @@
 // bf16 GEMMs with both operands m/n-contiguous: the weight-gradient products
 // dW = X^T dY (reduction over tokens, fp32 accumulate into the gradient
 // buffers) and the attention products P^T dO, dS^T Q.
-#include "gemm_bf16_kernel.h"
+#include "gemm_bf16_tile.h"
 
 namespace {
 
@@ -29,13 +29,14 @@ __global__ __launch_bounds__(256) void colsum_rows_k(const float* __restrict__ w
 
 hipError_t gemm_bf16_tn(const GemmParams& p, hipStream_t s) {
   hipError_t e;
+  int rows = 0;
   switch (p.epi) {
-    case EPI_STORE: e = launch_bf16<false, false, EPI_STORE>(p, s); break;
-    case EPI_F32_ACC: e = launch_bf16<false, false, EPI_F32_ACC>(p, s); break;
+    case EPI_STORE: e = launch_bf16<false, false, EPI_STORE>(p, s, &rows); break;
+    case EPI_F32_ACC: e = launch_bf16<false, false, EPI_F32_ACC>(p, s, &rows); break;
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess || p.colsum_out == nullptr) return e;
   hipLaunchKernelGGL(colsum_rows_k, dim3((p.N + 255) / 256), dim3(256), 0, s, p.colsum_work,
-                     (p.M + 255) / 256, p.N, p.colsum_out, p.colsum_acc);
+                     rows, p.N, p.colsum_out, p.colsum_acc);
   return hipGetLastError();
 }

@@ -80,7 +80,8 @@ struct Layout {
   WLayer w;
   FLayer fl;
   size_t wslot_bytes, fslot_bytes, off_fslots, stash_bytes;
-  size_t off_S, off_dS, off_dO, off_dv, off_check, off_part, off_cswork, work_bytes;
+  size_t off_S, off_dS, off_dO, off_dv, off_check, off_part, off_cswork, off_split, work_bytes;
+  long split_floats, cs_floats;
   uint64_t acct_af, acct_sw;
 };
 
@@ -205,13 +206,42 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
     y.acct_af = (uint64_t)y.L * (E * (8 * Th + 2 * Tf) + st + attn);
     y.acct_sw = (uint64_t)y.L * (E * (12 * Th + 2 * Tf) + st);
   }
-  y.off_part = take(4 * colsum_part_floats(y.T, (int)std::max(3 * h, f),
-                                           std::min(y.wslots, (int)GEMM_MAX_SEG)));
-  // partial bias sums of the bf16 weight-gradient products (one product at a
-  // time): the largest of [h, 3h], [h, h], [h, f], [f, h]
-  y.off_cswork = take(y.bf ? 4 * std::max(gemm_colsum_floats(h, std::max(3 * h, f)), gemm_colsum_floats(f, h))
-                           : 0);
-  y.work_bytes = o;
+  // Work memory of the products: partials of split reductions (split_floats,
+  // taken where they fit) and partial bias sums of the bf16 weight-gradient
+  // products (one product at a time).
+  const int nw = std::min(y.wslots, (int)GEMM_MAX_SEG);
+  long want_split = 0;
+  y.cs_floats = 0;
+  {
+    auto product = [&](long M, long N, long nseg, long seg, bool wgrad) {
+      const GemmWork g = y.bf ? gemm_bf16_work(M, N, nseg, seg) : gemm_f32_work(M, N, nseg, seg);
+      want_split = std::max(want_split, g.split_floats);
+      if (wgrad && y.bf) y.cs_floats = std::max(y.cs_floats, g.colsum_floats);
+    };
+    const long shapes[4][2] = {{h, 3 * h}, {h, h}, {h, f}, {f, h}};  // [in, out] of the linear layers
+    for (auto& q : shapes) {
+      product(y.T, q[1], 1, q[0], false);  // Y = X W
+      product(y.T, q[0], 1, q[1], false);  // dX = dY W^T
+      for (int n = 1; n <= nw; ++n) product(q[0], q[1], n, y.T, true);  // dW = X^T dY of n micro-batches
+    }
+  }
+  // RC_STATIC_WORK_BYTES admits a configuration by what it needs without
+  // partials of split reductions, counted as part and cs below; those partials
+  // take the rest of that memory at most.
+  const size_t part = 4 * colsum_part_floats(y.T, (int)std::max(3 * h, f), nw);
+  const size_t cs = y.bf ? 4 * std::max((h + 255) / 256 * std::max(3 * h, f), (f + 255) / 256 * h) : 0;
+  const size_t need = align_up(o + part) + align_up(cs);
+  // bf16 stages reduce only h columns outside the products
+  y.off_part = take(y.bf ? 4 * colsum_part_floats(y.T, (int)h, nw) : part);
+  if (need <= RC_STATIC_WORK_BYTES && o + 4 * y.cs_floats > RC_STATIC_WORK_BYTES)
+    y.cs_floats = (long)(need - o) / 4;  // at least cs
+  y.off_cswork = take(4 * y.cs_floats);
+  y.off_split = o;
+  size_t total = std::max(need, align_up(o + 4 * want_split));
+  if (need <= RC_STATIC_WORK_BYTES) total = std::min(total, (size_t)RC_STATIC_WORK_BYTES);
+  total = std::max(total, o);
+  y.split_floats = std::min<long>(want_split, (total - o) / 4);
+  y.work_bytes = total;
   return RC_OK;
 }
 
@@ -346,7 +376,9 @@ GemmParams gp(int M, int N, int K, const void* A, long lda, int ak, const void* 
   return g;
 }
 
-hipError_t gemm(rc_stage* st, const GemmParams& g) {
+hipError_t gemm(rc_stage* st, GemmParams g) {
+  g.split_work = (float*)(st->work + st->lay.off_split);
+  g.split_floats = st->lay.split_floats;
   return st->lay.bf ? gemm_bf16(g, st->stream) : gemm_f32(g, st->stream);
 }
 
@@ -540,8 +572,6 @@ rc_status run_backward_weight(rc_stage* st, const int* ws, int n) {
   const int acc = st->grads_fresh ? 0 : 1;
   hipStream_t s = st->stream;
   float* part = (float*)(st->work + y.off_part);
-  // bf16 k-tiles of 64 must not straddle two micro-batches
-  const bool fused = !y.bf || (T % 64 == 0);
   for (int l = 0; l < y.L; ++l) {
     WPtr w[GEMM_MAX_SEG];
     for (int q = 0; q < n; ++q) w[q] = wptr(st, ws[q], l);
@@ -559,34 +589,21 @@ rc_status run_backward_weight(rc_stage* st, const int* ws, int n) {
                 {RC_P_W_2, RC_P_B_2, f, h, &WPtr::G, &WPtr::dY}};
     for (auto& q : lin) {
       // dW (+)= sum over the n micro-batches of X^T dY (reduction over tokens)
-      if (fused) {
-        GemmParams g = gp(q.M, q.N, T * n, nullptr, q.M, 0, nullptr, q.N, 0, EPI_F32_ACC,
-                          gradp(st, l, q.pid), q.N);
-        g.accumulate = acc;
-        if (y.bf) {
-          g.colsum_out = gradp(st, l, q.bpid);
-          g.colsum_acc = acc;
-          g.colsum_work = (float*)(st->work + y.off_cswork);
-        }
-        g.kseg_len = (int)T;
-        for (int k = 0; k < n; ++k) {
-          g.segA[k] = w[k].*(q.X);
-          g.segB[k] = w[k].*(q.dY);
-        }
-        HIPCHK(gemm_lin(st, g, RC_K_GEMM_WGRAD));
-      } else {
-        for (int k = 0; k < n; ++k) {
-          GemmParams g = gp(q.M, q.N, T, w[k].*(q.X), q.M, 0, w[k].*(q.dY), q.N, 0, EPI_F32_ACC,
-                            gradp(st, l, q.pid), q.N);
-          g.accumulate = acc || k > 0;
-          if (y.bf) {
-            g.colsum_out = gradp(st, l, q.bpid);
-            g.colsum_acc = g.accumulate;
-            g.colsum_work = (float*)(st->work + y.off_cswork);
-          }
-          HIPCHK(gemm_lin(st, g, RC_K_GEMM_WGRAD));
-        }
+      GemmParams g = gp(q.M, q.N, T * n, nullptr, q.M, 0, nullptr, q.N, 0, EPI_F32_ACC,
+                        gradp(st, l, q.pid), q.N);
+      g.accumulate = acc;
+      if (y.bf) {
+        g.colsum_out = gradp(st, l, q.bpid);
+        g.colsum_acc = acc;
+        g.colsum_work = (float*)(st->work + y.off_cswork);
+        g.colsum_floats = y.cs_floats;
       }
+      g.kseg_len = (int)T;
+      for (int k = 0; k < n; ++k) {
+        g.segA[k] = w[k].*(q.X);
+        g.segB[k] = w[k].*(q.dY);
+      }
+      HIPCHK(gemm_lin(st, g, RC_K_GEMM_WGRAD));
     }
     // Column sums: the LN parameters' gradients, and on the fp32 path also the
     // biases' (bytes: n micro-batches' inputs, then the gradient update).
