@@ -1,0 +1,10 @@
+// Fused attention kernels of 96 columns (head dimensions up to 96).
+#include "attn_flash.h"
+#include "attn_flash_kernels.h"
+
+hipError_t attn_fwd_96(const AttnArgs& a, int causal, bool paired, hipStream_t st) {
+  return attn_fwd_launch<96, false>(a, causal, paired, st);
+}
+hipError_t attn_bwd_96(const AttnArgs& a, int causal, bool paired, hipStream_t st) {
+  return attn_bwd_launch<96, false>(a, causal, paired, st);
+}

@@ -43,14 +43,17 @@ hipError_t softmax_forward(int elt, const float* S, void* P, long rows, int s, f
 hipError_t softmax_backward(int elt, const float* dP, const void* P, void* dS, long rows, int s,
                             float scale, int causal, hipStream_t st);
 
-// Fused attention core (bf16, head dimension 128): per (sequence, head)
-// O = softmax(Q K^T / sqrt(128), causal) V without materialising the scores.
-// qkv: [b*s, 3h] with column blocks Q | K | V (head j at columns j*128 of each);
+// Fused attention core (bf16, head dimension d <= 128): per (sequence, head)
+// O = softmax(Q K^T / sqrt(d), causal) V without materialising the scores.
+// qkv: [b*s, 3h] with column blocks Q | K | V (head j at columns j*d of each);
 // o: [b*s, h]; lse: [b, heads, s] fp32 base-2 log-sum-exp of the scaled scores
 // (written by the forward, read by the backward).  The backward writes dQ, dK,
 // dV into the three column blocks of dqkv [b*s, 3h]; dv_scratch holds b*heads*s
-// floats.  h == heads * 128.
-bool attn_flash_supported(int elt, int head_dim);
+// floats.  h == heads * d.  Head dimensions other than 128 take it for
+// sequences of more than one query block (128); up to that the materialised
+// kernels stay, whose probabilities are small there, as stages of short
+// sequences and narrow heads report through rc_stage_attention_kernels.
+bool attn_flash_supported(int elt, int head_dim, int s);
 // Whether causal fused attention over b sequences of s tokens and `heads`
 // heads runs the paired kernels (one workgroup per pair of query blocks) on
 // the current device, rather than one workgroup per query block.

@@ -110,7 +110,7 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
                                       "exceeds 2^31-1 bytes");
     if (2L * c->hidden * wide > cap)
       return fail(RC_ERR_UNSUPPORTED, "bf16 weight matrix [hidden, max(3*hidden, ffn)] exceeds 2^31-1 bytes");
-    if (!attn_flash_supported(2, d) && 2L * c->seq_len * c->seq_len > cap)
+    if (d != 128 && 2L * c->seq_len * c->seq_len > cap)
       return fail(RC_ERR_UNSUPPORTED, "bf16 attention probabilities [seq_len, seq_len] of one head "
                                       "exceed 2^31-1 bytes");
   }
@@ -124,7 +124,7 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
   y.T = (long)c->micro_batch * c->seq_len;
   y.bf = c->dtype == RC_BF16;
   y.elt = y.bf ? 2 : 4;
-  y.flash = attn_flash_supported(y.elt, d);
+  y.flash = attn_flash_supported(y.elt, d, c->seq_len);
   y.causal = c->causal;
   y.eps = c->ln_eps;
   y.wslots = c->max_stashed_mb;
@@ -202,7 +202,10 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
   // B_weight the whole weight-pass slot.
   {
     const uint64_t Th = (uint64_t)T * h, Tf = (uint64_t)T * f, st = 16ull * T;
-    const uint64_t attn = y.flash ? 4ull * rows : (uint64_t)E * ss;
+    // Head dimensions other than 128 count the probabilities also where the
+    // fused kernels keep only the row statistics, so that limits and op lists
+    // planned with these figures stay valid whichever kernels run.
+    const uint64_t attn = y.bf && d == 128 ? 4ull * rows : (uint64_t)E * ss;
     y.acct_af = (uint64_t)y.L * (E * (8 * Th + 2 * Tf) + st + attn);
     y.acct_sw = (uint64_t)y.L * (E * (12 * Th + 2 * Tf) + st);
   }

@@ -1,0 +1,85 @@
+"""Parity of whole stages at shapes where tiles, splits and head widths end:
+every product and attention kernel variant that the launchers choose by size,
+against the fp64 oracle.  Bars are those of tests/test_gpu_parity.py (rel-L2
+<= 1e-5 for fp32 stages, 2e-2 for bf16 ones); the small rows of a head of 8 or
+32 sum fewer terms than the shapes those bars were set for."""
+import pytest
+
+import oracle
+from synth import get_config
+from tests.conftest import compare_grads, rel_l2
+from tests.gpu_harness import log, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+
+
+def check(cfg, t):
+    log(f"[shape] L={cfg.layers} h={cfg.hidden} a={cfg.heads} f={cfg.ffn} s={cfg.seq} b={cfg.micro_batch} "
+        f"n={cfg.n_mb} {cfg.dtype} causal={cfg.causal}")
+    g = run_gpu(cfg)
+    o = oracle.run_oplist(cfg)
+    assert g.log == [tuple(r) for r in o.stage.log]
+    for mb in o.y:
+        assert rel_l2(g.y[mb], o.y[mb]) < t, ("y", mb, rel_l2(g.y[mb], o.y[mb]))
+        assert rel_l2(g.dx[mb], o.dx[mb]) < t, ("dx", mb, rel_l2(g.dx[mb], o.dx[mb]))
+    log(f"[shape] worst gradient rel-L2 {compare_grads(cfg, g.grads, o.grads, t):.2e}")
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d,seq", [(8, 136), (32, 200), (40, 328), (64, 136), (64, 520), (80, 328), (96, 136),
+                                   (104, 328), (120, 200), (64, 128)])
+def test_attention_head_widths(d, seq, causal):
+    """Head dimensions below 128, with as many columns as a kernel is compiled
+    for and fewer; ragged last query and key blocks; d = 64 at s = 128 takes
+    the materialised kernels."""
+    cfg = get_config("small_bf16").with_(layers=1, hidden=4 * d, heads=4, ffn=16 * d, seq=seq, n_mb=2,
+                                         rerouted=(1,), causal=causal)
+    check(cfg, 2e-2)
+
+
+@pytest.mark.parametrize("d", [64, 80])
+def test_attention_head_widths_per_block(d):
+    """The per-query-block causal kernels of narrow heads: the grid of pairs
+    would fill the compute units poorly."""
+    from paper_2405_14009_amd import Stage
+    cfg = get_config("block_bf16").with_(hidden=10 * d, ffn=20 * d, seq=1000, n_mb=1, rerouted=())
+    stage = Stage.from_config(cfg, dry_run=True)
+    assert stage.attention_kernels() == "block"
+    check(cfg, 2e-2)
+
+
+# Token counts and widths one chunk of 8 to either side of 64, 128 and 256, a
+# single k-tile and long reductions; several micro-batches whose token counts
+# are no multiple of a k-tile.
+SHAPES = [dict(hidden=64, heads=1, ffn=64, seq=64, micro_batch=1, n_mb=1),
+          dict(hidden=56, heads=1, ffn=72, seq=8, micro_batch=1, n_mb=2),
+          dict(hidden=136, heads=1, ffn=264, seq=72, micro_batch=1, n_mb=3),
+          dict(hidden=256, heads=2, ffn=2048, seq=248, micro_batch=1, n_mb=2),
+          dict(hidden=264, heads=3, ffn=1032, seq=1000, micro_batch=3, n_mb=3),
+          dict(hidden=512, heads=4, ffn=4096, seq=56, micro_batch=1, n_mb=5)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_product_shapes(dtype, shape):
+    cfg = get_config("small_bf16").with_(layers=1, dtype=dtype, rerouted=(), schedule="1f1b_deferred_w", **shape)
+    check(cfg, 1e-5 if dtype == "f32" else 2e-2)
+
+
+def test_split_products_are_reproducible():
+    """Partials of split reductions are added in a fixed order: the same
+    iteration twice gives the same bits."""
+    import numpy as np
+    cfg = get_config("small_bf16").with_(layers=1, hidden=512, heads=4, ffn=4096, seq=328, n_mb=4, rerouted=())
+    a, b = run_gpu(cfg), run_gpu(cfg)
+    for mb in a.y:
+        assert np.array_equal(a.y[mb], b.y[mb]) and np.array_equal(a.dx[mb], b.dx[mb])
+    for p in range(12):
+        assert np.array_equal(a.grads[0][p], b.grads[0][p]), p
