@@ -73,6 +73,37 @@ __device__ __forceinline__ float block_max(float v, float* red) {
   return s;
 }
 
+// 16-byte chunks of a row.
+template <class E>
+struct Chunk {
+  static constexpr int N = 16 / sizeof(E);  // elements per 16-byte chunk
+};
+
+__device__ __forceinline__ void unpack(const uint4& u, const bf16*, float (&f)[8]) {
+  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f[2 * i] = __uint_as_float(w[i] << 16);
+    f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+  }
+}
+__device__ __forceinline__ void unpack(const uint4& u, const float*, float (&f)[4]) {
+  f[0] = __uint_as_float(u.x);
+  f[1] = __uint_as_float(u.y);
+  f[2] = __uint_as_float(u.z);
+  f[3] = __uint_as_float(u.w);
+}
+__device__ __forceinline__ uint4 pack(const float (&f)[8], const bf16*) {
+  bf16 t[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) t[i] = (bf16)f[i];
+  return *(const uint4*)t;
+}
+__device__ __forceinline__ uint4 pack(const float (&f)[4], const float*) {
+  return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]),
+                    __float_as_uint(f[3]));
+}
+
 // Compute units of the current device (host; cached per device, 256 when the
 // query fails).
 inline int device_compute_units() {

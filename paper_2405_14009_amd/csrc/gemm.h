@@ -52,14 +52,13 @@ struct GemmParams {
   // bias gradient of a linear layer is exactly this sum of its output
   // gradient, the B operand of its weight-gradient product.  The workgroup of
   // tile-row tm sums the B tiles it stages anyway whose k-tile index t has
-  // t mod tiles_m == tm, into row tm of colsum_work (GemmWork::colsum_floats
-  // floats; split s of a split reduction into row s * tiles_m + tm); a second
-  // kernel adds the rows in a fixed order and writes (colsum_acc: adds) them to
-  // colsum_out[0, N) in fp32.  nullptr: off.
-  float* colsum_out;
-  int colsum_acc;
+  // t mod tiles_m == tm, into row tm of colsum_work ([rows, N] floats of the
+  // colsum_floats there; split s of a split reduction into row
+  // s * tiles_m + tm).  Adding up the rows is the caller's (colsum); their
+  // number is returned in *colsum_rows.  nullptr: off.
   float* colsum_work;
   long colsum_floats;
+  int* colsum_rows;
   // Split reductions: with splits > 1 (set by the launchers, which also point
   // C at the partials) workgroup row blockIdx.y multiplies k in
   // [y * split_k, (y + 1) * split_k) and stores its fp32 partial of the whole

@@ -384,6 +384,46 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// Operands of the k-tiles in turn: descriptors and k-range of the current one.
+// Only weight-gradient products (both operands m/n-contiguous) are segmented.
+// A segmented reduction changes descriptors at its segment ends only (looking
+// the segment up for every k-tile put an integer division and two scalar loads,
+// whose wait also waits for the wave's LDS reads, into every k-tile; a k-tile
+// never straddles segments).
+template <bool AK, bool BKC, int BK>
+struct KWalk {
+  static constexpr bool SEG = !AK && !BKC;
+  i32x4 a, b;
+  int k, kend, sg;
+  __device__ __forceinline__ void set(const GemmParams& p, const void* A, const void* B, long a_off, long b_off,
+                                      int rows) {
+    a = make_rsrc((const bf16*)A + a_off, 2L * (AK ? (long)p.M * p.lda : (long)rows * p.lda));
+    b = make_rsrc((const bf16*)B + b_off, 2L * (BKC ? (long)p.N * p.ldb : (long)rows * p.ldb));
+  }
+  // first k-tile at k0, a multiple of BK; unsegmented reductions end at ke
+  __device__ __forceinline__ void init(const GemmParams& p, long a_off, long b_off, int k0, int ke) {
+    k = k0;
+    kend = ke;
+    sg = 0;
+    if (SEG && p.kseg_len > 0) {
+      sg = k0 / p.kseg_pad;
+      k = k0 - sg * p.kseg_pad;
+      kend = p.kseg_len;
+      if (k0 < p.K) set(p, p.segA[sg], p.segB[sg], a_off, b_off, p.kseg_len);
+    } else {
+      set(p, p.A, p.B, a_off, b_off, p.K);
+    }
+  }
+  __device__ __forceinline__ void next(const GemmParams& p, long a_off, long b_off) {
+    k += BK;
+    if (SEG && p.kseg_len > 0 && k >= p.kseg_pad) {
+      k = 0;
+      ++sg;
+      if (sg * p.kseg_pad < p.K) set(p, p.segA[sg], p.segB[sg], a_off, b_off, p.kseg_len);
+    }
+  }
+};
+
 template <int BM, int BN, int NW, int KS, int BK, int NST, bool AK, bool BKC, int EPI>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   // the configuration the launcher uses (256 x 128 tiles run the ping-pong
@@ -428,11 +468,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   const int split = p.splits > 1 ? blockIdx.y : 0;
   const int z = p.splits > 1 ? 0 : blockIdx.y;
   const int zb = z / p.heads, zh = z % p.heads;
-  const bf16* A = (const bf16*)p.A + zb * p.a_bs + zh * p.a_hs;
-  const bf16* B = (const bf16*)p.B + zb * p.b_bs + zh * p.b_hs;
+  const long a_off = zb * p.a_bs + zh * p.a_hs, b_off = zb * p.b_bs + zh * p.b_hs;
   const long c_off = p.splits > 1 ? (long)split * p.M * p.N : zb * p.c_bs + zh * p.c_hs;
-  const i32x4 ra = make_rsrc(A, 2L * (AK ? (long)p.M * p.lda : (long)p.K * p.lda));
-  const i32x4 rb = make_rsrc(B, 2L * (BKC ? (long)p.N * p.ldb : (long)p.K * p.ldb));
 
   int kb = 0, ke = p.K;
   if (p.krange == KR_BELOW) ke = min(p.K, m0 + BM);
@@ -463,34 +500,17 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   constexpr bool CS = !AK && !BKC;  // weight-gradient layout only
   // Every tile-row takes part in the column sums for one k-tile in tiles_m, so
   // the extra work spreads evenly over the launch.
-  const bool cs_on = CS && p.colsum_out != nullptr && z == 0;
+  const bool cs_on = CS && p.colsum_work != nullptr && z == 0;
   int cs_next = tm;  // next k-tile this workgroup sums
   ColSums<BN, BK> cs;
   if (cs_on) cs.init(threadIdx.x);
 
-  // Operands of the k-tile at k0: with a segmented reduction the k-tile's
-  // segment selects the operand bases (a k-tile never straddles segments).
-  struct Src {
-    i32x4 a, b;
-    int k, kend;
-  };
-  auto source = [&](int k0) {
-    Src r{ra, rb, k0, ke};
-    if (p.kseg_len > 0) {
-      const int sg = k0 / p.kseg_pad;
-      r.k = k0 - sg * p.kseg_pad;
-      r.kend = p.kseg_len;
-      r.a = make_rsrc((const bf16*)p.segA[sg] + zb * p.a_bs + zh * p.a_hs,
-                      2L * (AK ? (long)p.M * p.lda : (long)p.kseg_len * p.lda));
-      r.b = make_rsrc((const bf16*)p.segB[sg] + zb * p.b_bs + zh * p.b_hs,
-                      2L * (BKC ? (long)p.N * p.ldb : (long)p.kseg_len * p.ldb));
-    }
-    return r;
-  };
-  auto issue = [&](char* st, int k0) {
-    const Src sr = source(k0);
-    ca.issue(sr.a, st, wave, p.lda, p.M, sr.k, sr.kend);
-    cb.issue(sr.b, st + A_BYTES, wave, p.ldb, p.N, sr.k, sr.kend);
+  KWalk<AK, BKC, BK> wk;  // the next k-tile to copy
+  wk.init(p, a_off, b_off, kb, ke);
+  auto issue = [&](char* st) {
+    ca.issue(wk.a, st, wave, p.lda, p.M, wk.k, wk.kend);
+    cb.issue(wk.b, st + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
+    wk.next(p, a_off, b_off);
   };
   // Ring of NST stages: tile t lives in stage t mod NST.  Tiles 0 .. NST-2 are
   // issued up front; iteration t waits for tile t, publishes it with the
@@ -507,7 +527,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   mma_pending_clear<4, TN>(pa, pb);
 #pragma unroll
   for (int i = 0; i < NST - 1; ++i)
-    if (i < nk) issue(lds + i * STAGE, kb + i * BK);
+    if (i < nk) issue(lds + i * STAGE);
   int sc = 0, si = NST - 1;  // stage of tile t, stage that tile t + NST - 1 goes to
   for (int t = 0; t < nk; ++t) {
     __builtin_amdgcn_sched_barrier(0);
@@ -516,13 +536,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
     const bool refill = t + NST - 1 < nk;
-    const Src nx = source(refill ? kb + (t + NST - 1) * BK : kb);
     char* dst = lds + si * STAGE;
     const char* st = lds + sc * STAGE;
     mma_tile<BM, BN, AK, BKC, 4, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
-      if (refill && ks == 0) ca.issue(nx.a, dst, wave, p.lda, p.M, nx.k, nx.kend);
-      if (refill && ks == 1) cb.issue(nx.b, dst + A_BYTES, wave, p.ldb, p.N, nx.k, nx.kend);
+      if (refill && ks == 0) ca.issue(wk.a, dst, wave, p.lda, p.M, wk.k, wk.kend);
+      if (refill && ks == 1) cb.issue(wk.b, dst + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
     }, pa, pb);
+    if (refill) wk.next(p, a_off, b_off);
     if constexpr (CS) {
       // while the tile's MFMAs drain; the stage stays valid until the next barrier
       __builtin_amdgcn_sched_barrier(0);
@@ -588,10 +608,6 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
     n0 = ((pid % width) / gsz) * BN;
   };
 
-  const bf16* A = (const bf16*)p.A;
-  const bf16* B = (const bf16*)p.B;
-  const i32x4 ra = make_rsrc(A, 2L * (AK ? (long)p.M * p.lda : (long)p.K * p.lda));
-  const i32x4 rb = make_rsrc(B, 2L * (BKC ? (long)p.N * p.ldb : (long)p.K * p.ldb));
   const int nk = (p.K + BK - 1) / BK;
 
   Copier<BM, AK, NIA, NW, BK> ca;
@@ -600,28 +616,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
   FragOffsets<BN, BKC, TN, NKS, BK> fb;
   fa.init(wm * 128, lane, 0);
   fb.init(wn * (BN / WN_), lane, 0);
-  struct Src {
-    i32x4 a, b;
-    int k, kend;
-  };
-  auto source = [&](int k0) {
-    Src r{ra, rb, k0, p.K};
-    if (p.kseg_len > 0) {
-      const int sg = k0 / p.kseg_pad;
-      r.k = k0 - sg * p.kseg_pad;
-      r.kend = p.kseg_len;
-      r.a = make_rsrc(p.segA[sg], 2L * (AK ? (long)p.M * p.lda : (long)p.kseg_len * p.lda));
-      r.b = make_rsrc(p.segB[sg], 2L * (BKC ? (long)p.N * p.ldb : (long)p.kseg_len * p.ldb));
-    }
-    return r;
-  };
-  auto issue = [&](char* st, int k0) {
-    const Src sr = source(k0);
-    ca.issue(sr.a, st, wave, p.lda, p.M, sr.k, sr.kend);
-    cb.issue(sr.b, st + A_BYTES, wave, p.ldb, p.N, sr.k, sr.kend);
+  KWalk<AK, BKC, BK> wk;  // the next k-tile to copy
+  auto issue_first = [&](char* st) {
+    wk.init(p, 0, 0, 0, p.K);
+    ca.issue(wk.a, st, wave, p.lda, p.M, wk.k, wk.kend);
+    cb.issue(wk.b, st + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
+    wk.next(p, 0, 0);
   };
   constexpr bool CS = !AK && !BKC;
-  const bool cs_on = CS && p.colsum_out != nullptr;
+  const bool cs_on = CS && p.colsum_work != nullptr;
 
   int i = blockIdx.x >> 3;
   if (i >= nx) return;
@@ -629,7 +632,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
   tile_of(i, m0, n0, tm);
   ca.init(wave, p.lda, m0, lane);
   cb.init(wave, p.ldb, n0, lane);
-  if (nk > 0) issue(lds, 0);
+  if (nk > 0) issue_first(lds);
   f32x16 acc[4][TN];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
@@ -651,13 +654,13 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
       __builtin_amdgcn_sched_barrier(0);
       // refill split over the first two k-steps as in gemm_bf16_kernel
       const bool refill = t + 1 < nk;
-      const Src nx = source(refill ? (t + 1) * BK : 0);
       char* dst = lds + si * STAGE;
       const char* st = lds + sc * STAGE;
       mma_tile<BM, BN, AK, BKC, 4, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
-        if (refill && ks == 0) ca.issue(nx.a, dst, wave, p.lda, p.M, nx.k, nx.kend);
-        if (refill && ks == 1) cb.issue(nx.b, dst + A_BYTES, wave, p.ldb, p.N, nx.k, nx.kend);
+        if (refill && ks == 0) ca.issue(wk.a, dst, wave, p.lda, p.M, wk.k, wk.kend);
+        if (refill && ks == 1) cb.issue(wk.b, dst + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
       }, pa, pb);
+      if (refill) wk.next(p, 0, 0);
       if constexpr (CS) {
         __builtin_amdgcn_sched_barrier(0);
         if (cs_on && t == cs_next) {
@@ -677,7 +680,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
       tile_of(inext, m0, n0, tm);
       ca.init(wave, p.lda, m0, lane);
       cb.init(wave, p.ldb, n0, lane);
-      if (nk > 0) issue(lds, 0);
+      if (nk > 0) issue_first(lds);
     }
     char* above = lds + STAGE;
     if constexpr (CS) {
@@ -815,11 +818,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
   const int split = p.splits > 1 ? blockIdx.y : 0;
   const int z = p.splits > 1 ? 0 : blockIdx.y;
   const int zb = z / p.heads, zh = z % p.heads;
-  const bf16* A = (const bf16*)p.A + zb * p.a_bs + zh * p.a_hs;
-  const bf16* B = (const bf16*)p.B + zb * p.b_bs + zh * p.b_hs;
+  const long a_off = zb * p.a_bs + zh * p.a_hs, b_off = zb * p.b_bs + zh * p.b_hs;
   const long c_off = p.splits > 1 ? (long)split * p.M * p.N : zb * p.c_bs + zh * p.c_hs;
-  const i32x4 ra = make_rsrc(A, 2L * (AK ? (long)p.M * p.lda : (long)p.K * p.lda));
-  const i32x4 rb = make_rsrc(B, 2L * (BKC ? (long)p.N * p.ldb : (long)p.K * p.ldb));
 
   int kb = 0, ke = p.K;
   if (p.krange == KR_BELOW) ke = min(p.K, m0 + BM);
@@ -850,32 +850,17 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
   constexpr bool CS = !AK && !BKC;  // weight-gradient layout only
   // Every tile-row takes part in the column sums for one k-tile in tiles_m, so
   // the extra work spreads evenly over the launch.
-  const bool cs_on = CS && p.colsum_out != nullptr && z == 0;
+  const bool cs_on = CS && p.colsum_work != nullptr && z == 0;
   int cs_next = tm;  // next k-tile this workgroup sums
   ColSums<BN, BK> cs;
   if (cs_on) cs.init(threadIdx.x);
 
-  struct Src {
-    i32x4 a, b;
-    int k, kend;
-  };
-  auto source = [&](int k0) {
-    Src r{ra, rb, k0, ke};
-    if (p.kseg_len > 0) {
-      const int sg = k0 / p.kseg_pad;
-      r.k = k0 - sg * p.kseg_pad;
-      r.kend = p.kseg_len;
-      r.a = make_rsrc((const bf16*)p.segA[sg] + zb * p.a_bs + zh * p.a_hs,
-                      2L * (AK ? (long)p.M * p.lda : (long)p.kseg_len * p.lda));
-      r.b = make_rsrc((const bf16*)p.segB[sg] + zb * p.b_bs + zh * p.b_hs,
-                      2L * (BKC ? (long)p.N * p.ldb : (long)p.kseg_len * p.ldb));
-    }
-    return r;
-  };
-  auto issue = [&](char* st, int k0) {
-    const Src sr = source(k0);
-    ca.issue(sr.a, st, wave, p.lda, p.M, sr.k, sr.kend);
-    cb.issue(sr.b, st + A_BYTES, wave, p.ldb, p.N, sr.k, sr.kend);
+  KWalk<AK, BKC, BK> wk;  // the next k-tile to copy
+  wk.init(p, a_off, b_off, kb, ke);
+  auto issue = [&](char* st) {
+    ca.issue(wk.a, st, wave, p.lda, p.M, wk.k, wk.kend);
+    cb.issue(wk.b, st + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
+    wk.next(p, a_off, b_off);
   };
   // The refill's A slices follow the unit's fragment reads.  Its B slices go
   // out between the compute phase's two k-steps when the B tiles are
@@ -896,7 +881,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
   // Prologue: tiles 0 .. NST-2 land before either group starts.
 #pragma unroll
   for (int i = 0; i < NST - 1; ++i)
-    if (i < nk) issue(lds + i * STAGE, kb + i * BK);
+    if (i < nk) issue(lds + i * STAGE);
   wait_vmcnt<0>();
   __syncthreads();
   if (grp == 1) phase_barrier();
@@ -910,10 +895,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
       // memory phase
       const bool refill = u == 0 && t + NST - 1 < nk;
       char* dst = lds + si * STAGE;
-      const Src nx = source(refill ? kb + (t + NST - 1) * BK : kb);
-      if (!SPLIT && refill) cb.issue(nx.b, dst + A_BYTES, wave, p.ldb, p.N, nx.k, nx.kend);
+      if (!KWalk<AK, BKC, BK>::SEG) wk.k = refill ? kb + (t + NST - 1) * BK : kb;
+      if (!SPLIT && refill) cb.issue(wk.b, dst + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
       load_unit<BM, BN, AK, BKC, TN, NKS, BK>(af, bfr, st, st + A_BYTES, fa, fb, u);
-      if (refill) ca.issue(nx.a, dst, wave, p.lda, p.M, nx.k, nx.kend);
+      if (refill) ca.issue(wk.a, dst, wave, p.lda, p.M, wk.k, wk.kend);
       if constexpr (CS) {
         if (u == 0 && cs_on && t == cs_next) {
           cs.tile(st + A_BYTES);
@@ -925,8 +910,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
       phase_barrier();
       // compute phase
       mma_unit<TN, SPLIT>(acc, af, bfr, [&]() {
-        if (refill) cb.issue(nx.b, dst + A_BYTES, wave, p.ldb, p.N, nx.k, nx.kend);
+        if (refill) cb.issue(wk.b, dst + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
       });
+      if (KWalk<AK, BKC, BK>::SEG && refill) wk.next(p, a_off, b_off);
       if (grp == 0 && u == U - 1) wait_next(t, false);
       phase_barrier();
     }

@@ -17,11 +17,13 @@ static hipError_t gemm_bf16_nn(const GemmParams& p, hipStream_t s) {
 
 hipError_t gemm_bf16(const GemmParams& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0 || p.batch * p.heads <= 0) return hipSuccess;
-  if (p.kseg_len > 0 && (p.K % p.kseg_len || p.K / p.kseg_len > GEMM_MAX_SEG || p.krange != KR_FULL))
+  // only weight-gradient products are segmented
+  if (p.kseg_len > 0 && (p.K % p.kseg_len || p.K / p.kseg_len > GEMM_MAX_SEG || p.krange != KR_FULL ||
+                         p.a_kcontig || p.b_kcontig))
     return hipErrorInvalidValue;
   if (p.a_kcontig && !p.b_kcontig) return gemm_bf16_nn(p, s);
   // column sums of B: weight-gradient layout only, with its workspace
-  if (p.colsum_out != nullptr && (p.a_kcontig || p.b_kcontig || p.colsum_work == nullptr || p.batch * p.heads != 1))
+  if (p.colsum_work != nullptr && (p.a_kcontig || p.b_kcontig || p.colsum_rows == nullptr || p.batch * p.heads != 1))
     return hipErrorInvalidValue;
   if (p.a_kcontig && p.b_kcontig) return gemm_bf16_nt(p, s);
   if (!p.a_kcontig && !p.b_kcontig) return gemm_bf16_tn(p, s);

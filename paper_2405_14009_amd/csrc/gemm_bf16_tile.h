@@ -44,8 +44,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(GemmParams p) {
   const int zb = z / p.heads, zh = z % p.heads;
   const long a_off = zb * p.a_bs + zh * p.a_hs, b_off = zb * p.b_bs + zh * p.b_hs;
   const long c_off = p.splits > 1 ? (long)split * p.M * p.N : zb * p.c_bs + zh * p.c_hs;
-  const i32x4 ra = make_rsrc((const bf16*)p.A + a_off, 2L * (AK ? (long)p.M * p.lda : (long)p.K * p.lda));
-  const i32x4 rb = make_rsrc((const bf16*)p.B + b_off, 2L * (BKC ? (long)p.N * p.ldb : (long)p.K * p.ldb));
   int kb = 0, ke = p.K;
   if (p.krange == KR_BELOW) ke = min(p.K, m0 + BM);
   else if (p.krange == KR_ABOVE) kb = (m0 / BK) * BK;
@@ -73,38 +71,62 @@ __global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(GemmParams p) {
   // Column sums of B (bias gradients): tile-row tm takes the k-tiles t of its
   // split with t mod tiles_m == tm, into row split * tiles_m + tm.
   constexpr bool CS = !AK && !BKC;
-  const bool cs_on = CS && p.colsum_out != nullptr && z == 0;
+  const bool cs_on = CS && p.colsum_work != nullptr && z == 0;
   int cs_next = tm;
   ColSums<BN, BK, 256> cs;
   if (cs_on) cs.init(threadIdx.x);
 
-  auto issue = [&](char* st, int k0) {
-    i32x4 a = ra, b = rb;
-    int k = k0, kend = ke;
-    if (p.kseg_len > 0) {
-      const int sg = k0 / p.kseg_pad;
-      k = k0 - sg * p.kseg_pad;
-      kend = p.kseg_len;
-      a = make_rsrc((const bf16*)p.segA[sg] + a_off, 2L * (AK ? (long)p.M * p.lda : (long)kend * p.lda));
-      b = make_rsrc((const bf16*)p.segB[sg] + b_off, 2L * (BKC ? (long)p.N * p.ldb : (long)kend * p.ldb));
-    }
-    ca.issue(a, st, wave, p.lda, p.M, k, kend);
-    cb.issue(b, st + A_BYTES, wave, p.ldb, p.N, k, kend);
+  KWalk<AK, BKC, BK> wk;  // the next k-tile to copy
+  wk.init(p, a_off, b_off, kb, ke);
+  auto issue = [&](char* st) {
+    ca.issue(wk.a, st, wave, p.lda, p.M, wk.k, wk.kend);
+    cb.issue(wk.b, st + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
+    wk.next(p, a_off, b_off);
   };
+  // Iteration t waits for its own copies of tile t, publishes them with the
+  // barrier, refills the stage of tile t - 1 and requests tile t's fragments.
+  // 64x64 tiles (two MFMAs' worth of fragments per k-step and wave) multiply
+  // tile t - 1 from registers meanwhile, whose fragment reads must then be
+  // complete at the barrier; 128x128 tiles multiply tile t, one k-step behind
+  // its reads.
+  constexpr bool AHEAD = TM * TN == 1;
+  bf16x8 fra[2][AHEAD ? NKS : 1], frb[2][AHEAD ? NKS : 1];
   bf16x8 pa[TM], pb[TN];  // (no deferred products here)
+  f32x16 acc2;  // the odd k-steps' sums: products that each wait for the one before leave gaps
+  if constexpr (AHEAD) {
 #pragma unroll
-  for (int i = 0; i < NST - 1; ++i)
-    if (i < nk) issue(lds + i * STAGE, kb + i * BK);
+    for (int r = 0; r < 16; ++r) acc2[r] = 0.f;
+  }
+  auto products = [&](int set) {
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int ks = 0; ks < NKS; ks += 2) {
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fra[set][ks], frb[set][ks], acc[0][0], 0, 0, 0);
+        acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fra[set][ks + 1], frb[set][ks + 1], acc2, 0, 0, 0);
+      }
+    }
+  };
   int sc = 0, si = NST - 1;
-  for (int t = 0; t < nk; ++t) {
+  auto step = [&](int t, int set) {
     __builtin_amdgcn_sched_barrier(0);
     if (t + NST - 2 < nk) wait_vmcnt<(NST - 2) * PER_TILE>();
     else wait_vmcnt<0>();
+    if constexpr (AHEAD) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
-    if (t + NST - 1 < nk) issue(lds + si * STAGE, kb + (t + NST - 1) * BK);
+    if (t + NST - 1 < nk) issue(lds + si * STAGE);
     const char* st = lds + sc * STAGE;
-    mma_tile<BM, BN, AK, BKC, TM, TN, NKS, BK, false>(acc, st, st + A_BYTES, fa, fb, [](int) {}, pa, pb);
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        fra[set][ks] = frag(st, fa, 0, ks);
+        frb[set][ks] = frag(st + A_BYTES, fb, 0, ks);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (t > 0) products(set ^ 1);
+    } else {
+      mma_tile<BM, BN, AK, BKC, TM, TN, NKS, BK, false>(acc, st, st + A_BYTES, fa, fb, [](int) {}, pa, pb);
+    }
     if constexpr (CS) {
       __builtin_amdgcn_sched_barrier(0);
       if (cs_on && t == cs_next) {
@@ -114,6 +136,21 @@ __global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(GemmParams p) {
     }
     sc = sc + 1 == NST ? 0 : sc + 1;
     si = si + 1 == NST ? 0 : si + 1;
+  };
+#pragma unroll
+  for (int i = 0; i < NST - 1; ++i)
+    if (i < nk) issue(lds + i * STAGE);
+  for (int t = 0; t < nk; t += 2) {
+    step(t, 0);
+    if (t + 1 < nk) step(t + 1, 1);
+  }
+  if constexpr (AHEAD) {
+    if (nk > 0) {
+      if (nk & 1) products(0);
+      else products(1);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][0][r] += acc2[r];
   }
   __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
@@ -171,9 +208,8 @@ hipError_t launch_tiles(const GemmParams& p, const GemmPlan& pl, hipStream_t s) 
   return hipGetLastError();
 }
 
-// rows (optional): the number of partial column-sum rows written.
 template <bool AK, bool BKC, int EPI>
-hipError_t launch_bf16(GemmParams p, hipStream_t s, int* rows = nullptr) {
+hipError_t launch_bf16(GemmParams p, hipStream_t s) {
   if (p.kseg_len > 0) {  // every segment starts on a k-tile; its last one is padded with zeros
     const int nseg = p.K / p.kseg_len;
     p.kseg_pad = (p.kseg_len + 63) / 64 * 64;
@@ -183,9 +219,9 @@ hipError_t launch_bf16(GemmParams p, hipStream_t s, int* rows = nullptr) {
   const bool whole = z == 1 && p.krange == KR_FULL && !p.causal_skip;
   const int cus = device_compute_units();
   const GemmPlan pl = plan_bf16(p.M, p.N, p.K, z, whole && p.split_work ? p.split_floats : 0,
-                                p.colsum_out != nullptr ? p.colsum_floats : -1, cus);
-  if (p.colsum_out != nullptr && pl.colsum_rows(p.M) * p.N > p.colsum_floats) return hipErrorInvalidValue;
-  if (rows) *rows = (int)pl.colsum_rows(p.M);
+                                p.colsum_work != nullptr ? p.colsum_floats : -1, cus);
+  if (p.colsum_work != nullptr && pl.colsum_rows(p.M) * p.N > p.colsum_floats) return hipErrorInvalidValue;
+  if (p.colsum_work != nullptr) *p.colsum_rows = (int)pl.colsum_rows(p.M);
   p.splits = 1;
   if (pl.splits == 1) return launch_tiles<AK, BKC, EPI>(p, pl, s);
   GemmParams q = p;

@@ -2,79 +2,86 @@
 // and sums) for stages stored in fp32.  Same operand conventions, batching,
 // causal k-ranges and epilogues as the bf16 family.
 //
-// What bounds it: at ordinary sizes the matrix cores (256 flop per clock and
-// CU, 157 TFLOP/s nominal; a 64x64 tile draws 16 B/clk of operands per CU,
-// well below what the L2 delivers); at the smallest sizes the chain of
-// k-tiles of the few workgroups that the output has tiles for.  Hence
-//   * 64x64 tiles of four waves (one 32x32 MFMA block each), several
-//     workgroups per CU, so one's loads hide behind another's products;
-//   * k-tiles of 32 through registers into two LDS stages: tile t + 2 is
-//     requested while tile t is multiplied, tile t + 1 is written to LDS
-//     before the products of tile t, one barrier per k-tile;
-//   * reductions split over several workgroups where the output has few tiles.
-// LDS layouts.  k-contiguous operand: [row][k], rows padded to 36 floats, so
-// the 16-byte fragment reads of 16 consecutive rows fall on distinct banks.
-// m/n-contiguous operand: [k][row], k-rows padded by 8 floats, so the two
-// half-waves, which read k-rows 4 apart, use different banks.  MFMA e of a
-// group of four covers k = 8 g + e (lanes 0-31) and 8 g + 4 + e (lanes 32-63),
-// so a lane's four A (and B) values of a group are 4 consecutive k.
+// What bounds it: the matrix cores (256 flop per clock and CU, 157 TFLOP/s
+// nominal) at ordinary sizes, as long as the CU's operand stream keeps up (a
+// 64x64 tile draws 16 B/clk per CU at the full rate, which is most of what the
+// copies deliver, a 128x128 tile 8); the latency of the k-tile chain of the few
+// workgroups there are at the smallest sizes.  Hence 128x128 tiles of eight
+// waves where they fill the chip, else 64x64 tiles of four; k-tiles of 32
+// copied straight into a ring of LDS stages (buffer-load-to-LDS, up to
+// NST - 1 k-tiles in flight, one barrier each); and reductions split over
+// several workgroups where the output has few tiles.
+// LDS layouts, in 16-byte chunks.  k-contiguous operand: [row][32 k], chunk c
+// of row r at c ^ (r / 2 % 8): the fragment reads of 16 consecutive rows fall on
+// distinct banks.  m/n-contiguous operand: [k][row], chunk c of k-row k at
+// c ^ 8 (k / 4 % 2): the two half-waves, which read k-rows 4 apart, use
+// different banks.  MFMA e of a group of four covers k = 8 g + e (lanes 0-31)
+// and 8 g + 4 + e (lanes 32-63), so a lane's four A (and B) values of a group
+// are 4 consecutive k.
 #include "gemm.h"
 #include "gemm_plan.h"
+#include "mfma_common.h"
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr int TK = 32;
 
-constexpr int NT = 256, TK = 32;
+template <int N>
+__device__ __forceinline__ void wait_vm() {  // s_waitcnt vmcnt(N) alone
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
 
-// One operand of a k-tile: global -> registers -> LDS.
-template <int ROWS, bool KC>
+// One operand of a k-tile: this wave's 1 KB slices (of NW waves) and the
+// fragments of one row.
+template <int ROWS, bool KC, int NW>
 struct Operand {
-  static constexpr int STR = KC ? TK + 4 : ROWS + 8;           // floats per LDS row
-  static constexpr int FLOATS = KC ? ROWS * STR : TK * STR;    // per stage
-  static constexpr int CPR = KC ? TK / 4 : ROWS / 4;           // 16-byte chunks per LDS row
-  static constexpr int RPP = NT / CPR;                         // LDS rows per pass
-  static constexpr int NP = (KC ? ROWS : TK) / RPP;            // passes
-  float4 v[NP];
-  int r, c;
-  __device__ __forceinline__ void init(int tid) {
-    r = tid / CPR;
-    c = tid % CPR;
+  static constexpr int BYTES = ROWS * TK * 4;
+  static constexpr int ROWB = KC ? TK * 4 : ROWS * 4;  // bytes per LDS row
+  static constexpr int CPR = ROWB / 16, RPS = 64 / CPR;
+  static constexpr int NI = BYTES / 1024 / NW;
+  static_assert(BYTES % (1024 * NW) == 0, "copy split");
+  int r, c;  // LDS row of slice 0 and (swizzled back) chunk of this lane
+  __device__ __forceinline__ static int swz(int row) { return KC ? (row >> 1) & 7 : ((row >> 2) & 1) << 3; }
+  __device__ __forceinline__ void init(int wave, int lane) {
+    r = RPS * wave + lane / CPR;
+    c = (lane % CPR) ^ swz(r);  // the same for every slice of the wave
   }
-  // rows mn0.. (< MN) and k-range [k0, kend) of the matrix at p; zeros beyond
-  __device__ __forceinline__ void load(const float* p, long ld, int mn0, int MN, int k0, int kend) {
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const int mn = KC ? mn0 + r + RPP * i : mn0 + 4 * c;
-      const int k = KC ? k0 + 4 * c : k0 + r + RPP * i;
-      v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (mn < MN && k < kend) v[i] = *(const float4*)(p + (KC ? (long)mn * ld + k : (long)k * ld + mn));
-    }
+  // address of the tile at rows mn0 and k0 of the matrix at p, and the next k-tile's distance
+  __device__ __forceinline__ static const float* at(const float* p, long ld, int mn0, int k0) {
+    return KC ? p + (long)mn0 * ld + k0 : p + (long)k0 * ld + mn0;
   }
-  __device__ __forceinline__ void store(float* s) const {
-#pragma unroll
-    for (int i = 0; i < NP; ++i) *(float4*)(s + (r + RPP * i) * STR + 4 * c) = v[i];
+  __device__ __forceinline__ static long step(long ld) { return KC ? TK : TK * ld; }
+  // slice q of the tile there: rows mn0.. (< MN), k-range [k0, kend), zeros beyond
+  __device__ __forceinline__ void issue(const i32x4& rs, char* tile, long ld, int mn0, int MN, int k0, int kend,
+                                        int wave, int q) const {
+    const int row = r + RPS * NW * q;
+    const bool ok = KC ? (mn0 + row < MN && k0 + 4 * c < kend) : (k0 + row < kend && mn0 + 4 * c < MN);
+    const uint32_t off = ok ? (uint32_t)row * (uint32_t)(4 * ld) + 16u * c : kOOB;
+    dma16(rs, __builtin_amdgcn_readfirstlane(lds_addr(tile) + (wave + NW * q) * 1024), off);
   }
   // the four values of k-group g for row `row` of the tile, half-wave hf
-  __device__ __forceinline__ static void frag(const float* s, int row, int g, int hf, float (&f)[4]) {
+  __device__ __forceinline__ static void frag(const char* t, int row, int g, int hf, float (&f)[4]) {
     if constexpr (KC) {
-      const float4 t = *(const float4*)(s + row * STR + 8 * g + 4 * hf);
-      f[0] = t.x; f[1] = t.y; f[2] = t.z; f[3] = t.w;
+      const float4 v = *(const float4*)(t + row * ROWB + (((2 * g + hf) ^ swz(row)) << 4));
+      f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) f[e] = s[(8 * g + 4 * hf + e) * STR + row];
+      for (int e = 0; e < 4; ++e) {
+        const int k = 8 * g + 4 * hf + e;  // swz(k) = 8 hf
+        f[e] = *(const float*)(t + k * ROWB + (((row >> 2) ^ (hf << 3)) << 4) + 4 * (row & 3));
+      }
     }
   }
 };
 
-// Workgroup tile 64 WM x 64 WN: 2 x 2 waves of WM x WN MFMA blocks.
-template <int WM, int WN, bool AK, bool BKC, int EPI>
-__global__ __launch_bounds__(NT) void gemm_f32_kernel(GemmParams p) {
-  constexpr int BM = 64 * WM, BN = 64 * WN;
-  typedef Operand<BM, AK> OpA;
-  typedef Operand<BN, BKC> OpB;
-  constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
-  __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
+// Workgroup tile 64 WM x 32 WN NWN: 2 x NWN waves of WM x WN MFMA blocks.
+template <int WM, int WN, int NWN, int NST, bool AK, bool BKC, int EPI>
+__global__ __launch_bounds__(128 * NWN) void gemm_f32_kernel(GemmParams p) {
+  constexpr int BM = 64 * WM, BN = 32 * WN * NWN, NW = 2 * NWN;
+  typedef Operand<BM, AK, NW> OpA;
+  typedef Operand<BN, BKC, NW> OpB;
+  constexpr int STAGE = OpA::BYTES + OpB::BYTES, PER_TILE = OpA::NI + OpB::NI;
+  __shared__ __attribute__((aligned(1024))) char lds[NST * STAGE];
   const int tiles_m = (p.M + BM - 1) / BM;
   const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
@@ -92,70 +99,130 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(GemmParams p) {
   const int per_seg = p.kseg_len > 0 ? (p.kseg_len + TK - 1) / TK : 0;
   const int nk_all = p.kseg_len > 0 ? p.K / p.kseg_len * per_seg : (ke > kb ? (ke - kb + TK - 1) / TK : 0);
   const int t0 = p.splits > 1 ? split * (p.split_k / TK) : 0;
-  const int t1 = p.splits > 1 ? min(nk_all, t0 + p.split_k / TK) : nk_all;
+  const int nk = (p.splits > 1 ? min(nk_all, t0 + p.split_k / TK) : nk_all) - t0;
 
-  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, col = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int lane = threadIdx.x & 63, hf = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / NWN, wn = wave % NWN;
   OpA a;
   OpB b;
-  a.init(tid);
-  b.init(tid);
-  auto load = [&](int t) {
-    const float* pa = (const float*)p.A;
-    const float* pb = (const float*)p.B;
-    int k0 = kb + t * TK, kend = ke;
-    if (p.kseg_len > 0) {
-      const int sg = t / per_seg;
-      pa = (const float*)p.segA[sg];
-      pb = (const float*)p.segB[sg];
-      k0 = (t - sg * per_seg) * TK;
-      kend = p.kseg_len;
-    }
-    a.load(pa + a_off, p.lda, m0, p.M, k0, kend);
-    b.load(pb + b_off, p.ldb, n0, p.N, k0, kend);
+  a.init(wave, lane);
+  b.init(wave, lane);
+  // The next k-tile to copy: operand addresses, its k offset in its segment
+  // (or the whole range) and that one's end.
+  struct {
+    const float *a, *b;
+    int k0, kend, sg;
+  } wk;
+  auto at = [&](const void* A, const void* B) {
+    wk.a = OpA::at((const float*)A + a_off, p.lda, m0, wk.k0);
+    wk.b = OpB::at((const float*)B + b_off, p.ldb, n0, wk.k0);
   };
-  f32x16 acc[WM][WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  if (t0 < t1) {
-    load(t0);
-    a.store(lds);
-    b.store(lds + OpA::FLOATS);
-    if (t0 + 1 < t1) load(t0 + 1);
+  wk.sg = 0;
+  wk.k0 = kb + t0 * TK;
+  wk.kend = ke;
+  if (p.kseg_len > 0) {
+    wk.sg = t0 / per_seg;
+    wk.k0 = (t0 - wk.sg * per_seg) * TK;
+    wk.kend = p.kseg_len;
+    if (nk > 0) at(p.segA[wk.sg], p.segB[wk.sg]);
+  } else {
+    at(p.A, p.B);
   }
-  __syncthreads();
-  for (int t = t0; t < t1; ++t) {
-    const int cur = (t - t0) & 1;
-    const float* sa = lds + cur * STAGE;
-    const float* sb = sa + OpA::FLOATS;
-    if (t + 1 < t1) {  // the other stage was last read before the previous barrier
-      float* n = lds + (cur ^ 1) * STAGE;
-      a.store(n);
-      b.store(n + OpA::FLOATS);
-      if (t + 2 < t1) load(t + 2);
+  auto advance = [&] {
+    wk.k0 += TK;
+    wk.a += OpA::step(p.lda);
+    wk.b += OpB::step(p.ldb);
+    if (p.kseg_len > 0 && wk.k0 >= p.kseg_len) {
+      wk.k0 = 0;
+      ++wk.sg;
+      if (wk.sg * per_seg < nk_all) at(p.segA[wk.sg], p.segB[wk.sg]);
     }
+  };
+  auto issue = [&](char* st, int q) {  // slice q of the PER_TILE of a wave
+    if (q < OpA::NI) a.issue(make_rsrc(wk.a, 0x7fffffffL), st, p.lda, m0, p.M, wk.k0, wk.kend, wave, q);
+    else b.issue(make_rsrc(wk.b, 0x7fffffffL), st + OpA::BYTES, p.ldb, n0, p.N, wk.k0, wk.kend, wave, q - OpA::NI);
+  };
+  // Waves of a single block alternate between two accumulators: products that
+  // each wait for the one before leave gaps on the matrix core.
+  constexpr int NA = WM * WN == 1 ? 2 : 1;
+  f32x16 acc[NA][WM][WN];
 #pragma unroll
-    for (int g = 0; g < TK / 8; ++g) {
-      float fa[WM][4], fb[WN][4];
+  for (int n = 0; n < NA; ++n)
 #pragma unroll
-      for (int i = 0; i < WM; ++i) OpA::frag(sa, 32 * (wm * WM + i) + col, g, hf, fa[i]);
+    for (int i = 0; i < WM; ++i)
 #pragma unroll
-      for (int j = 0; j < WN; ++j) OpB::frag(sb, 32 * (wn * WN + j) + col, g, hf, fb[j]);
+      for (int j = 0; j < WN; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+        for (int r = 0; r < 16; ++r) acc[n][i][j][r] = 0.f;
+
+  // Tile i lives in stage i mod NST; iteration i waits for its own copies of
+  // tile i and for its fragment reads of tile i - 1, publishes the first and
+  // certifies the second with the barrier, requests the fragments of tile i and
+  // multiplies tile i - 1 from registers meanwhile, its copies into the stage
+  // that tile i - 1 left between the products: with few waves per SIMD the LDS
+  // latency and the copies' addresses would otherwise stand between every
+  // barrier and its products.
+  constexpr int NG = TK / 8;
+  static_assert(PER_TILE % NG == 0, "copies between the groups");
+  float fa[2][NG][WM][4], fb[2][NG][WN][4];
+  auto products = [&](int set, int g) {
 #pragma unroll
-        for (int i = 0; i < WM; ++i)
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int j = 0; j < WN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
-    }
+      for (int u = 0; u < WM; ++u)
+#pragma unroll
+        for (int v = 0; v < WN; ++v)
+          acc[e % NA][u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][g][u][e], fb[set][g][v][e],
+                                                                   acc[e % NA][u][v], 0, 0, 0);
+  };
+  int sc = 0, si = NST - 1;
+  auto step = [&](int i, int set) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + NST - 2 < nk) wait_vm<(NST - 2) * PER_TILE>();
+    else wait_vm<0>();
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    const char* ta = lds + sc * STAGE;
+    const char* tb = ta + OpA::BYTES;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+#pragma unroll
+      for (int q = 0; q < WM; ++q) OpA::frag(ta, 32 * (wm * WM + q) + col, g, hf, fa[set][g][q]);
+#pragma unroll
+      for (int q = 0; q < WN; ++q) OpB::frag(tb, 32 * (wn * WN + q) + col, g, hf, fb[set][g][q]);
+    }
+    const bool refill = i + NST - 1 < nk;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i > 0) products(set ^ 1, g);
+      __builtin_amdgcn_sched_barrier(0);
+      if (refill) {
+#pragma unroll
+        for (int q = 0; q < PER_TILE / NG; ++q) issue(lds + si * STAGE, g * (PER_TILE / NG) + q);
+      }
+    }
+    if (refill) advance();
+    sc = sc + 1 == NST ? 0 : sc + 1;
+    si = si + 1 == NST ? 0 : si + 1;
+  };
+#pragma unroll
+  for (int i = 0; i < NST - 1; ++i)
+    if (i < nk) {
+#pragma unroll
+      for (int q = 0; q < PER_TILE; ++q) issue(lds + i * STAGE, q);
+      advance();
+    }
+  for (int i = 0; i < nk; i += 2) {
+    step(i, 0);
+    if (i + 1 < nk) step(i + 1, 1);
+  }
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    if (nk > 0 && (nk & 1)) products(0, g);
+    if (nk > 0 && !(nk & 1)) products(1, g);
   }
 
   float* C = (float*)p.C + c_off;
@@ -163,7 +230,11 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(GemmParams p) {
   for (int i = 0; i < WM; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
-      const f32x16 v = acc[i][j];
+      f32x16 v = acc[0][i][j];
+      if constexpr (NA > 1) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] += acc[1][i][j][r];
+      }
       // lane: column col, rows 8 (r / 4) + 4 hf + r % 4.  The epilogue's inputs
       // of the whole block are requested before its stores.
       const int n = n0 + 32 * (wn * WN + j) + col;
@@ -208,44 +279,52 @@ __global__ __launch_bounds__(NT) void gemm_f32_kernel(GemmParams p) {
     }
 }
 
-template <int WM, int WN, bool AK, bool BKC, int EPI>
-hipError_t launch(GemmParams p, int splits, int split_k, hipStream_t s) {
-  const long tiles = (long)((p.M + 64 * WM - 1) / (64 * WM)) * ((p.N + 64 * WN - 1) / (64 * WN));
-  p.splits = splits;
-  if (splits == 1) {
-    hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, AK, BKC, EPI>), dim3(tiles, p.batch * p.heads), dim3(NT), 0, s, p);
-    return hipGetLastError();
-  }
-  GemmParams q = p;
-  q.split_k = split_k;
-  q.C = p.split_work;
-  q.ldc = p.N;
-  hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, AK, BKC, EPI_F32_STORE>), dim3(tiles, splits), dim3(NT), 0, s, q);
-  const hipError_t e = hipGetLastError();
-  return e != hipSuccess ? e : splitk_finish(4, p, s);
+template <bool AK, bool BKC, int EPI>
+hipError_t launch_tiles(const GemmParams& p, const F32Plan& pl, int y, hipStream_t s) {
+  const dim3 grid((unsigned)pl.tiles, (unsigned)y);
+  if (pl.bm == 128)
+    hipLaunchKernelGGL((gemm_f32_kernel<2, 1, 4, 4, AK, BKC, EPI>), grid, dim3(512), 0, s, p);
+  else
+    hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 2, 4, AK, BKC, EPI>), grid, dim3(256), 0, s, p);
+  return hipGetLastError();
 }
 
-template <int WM, int WN, bool AK, bool BKC>
+template <bool AK, bool BKC, int EPI>
+hipError_t launch(const GemmParams& p, const F32Plan& pl, hipStream_t s) {
+  GemmParams q = p;
+  q.splits = pl.splits;
+  if (pl.splits == 1) return launch_tiles<AK, BKC, EPI>(q, pl, p.batch * p.heads, s);
+  q.split_k = pl.split_k;
+  q.C = p.split_work;
+  q.ldc = p.N;
+  const hipError_t e = launch_tiles<AK, BKC, EPI_F32_STORE>(q, pl, pl.splits, s);
+  if (e != hipSuccess) return e;
+  q.C = p.C;
+  q.ldc = p.ldc;
+  return splitk_finish(4, q, s);
+}
+
+template <bool AK, bool BKC>
 hipError_t launch_epi(const GemmParams& p, hipStream_t s) {
   const bool whole = p.batch * p.heads == 1 && p.krange == KR_FULL && !p.causal_skip;
-  const long room = whole && p.split_work ? p.split_floats : 0;
-  const SplitPlan pl = plan_f32(p.M, p.N, p.kseg_len > 0 ? p.K / p.kseg_len : 1,
-                                p.kseg_len > 0 ? p.kseg_len : p.K, room, device_compute_units());
+  const F32Plan pl = plan_f32(p.M, p.N, p.kseg_len > 0 ? p.K / p.kseg_len : 1, p.kseg_len > 0 ? p.kseg_len : p.K,
+                              (long)p.batch * p.heads, whole && p.split_work ? p.split_floats : 0,
+                              device_compute_units());
   switch (p.epi) {
-    case EPI_STORE: return launch<WM, WN, AK, BKC, EPI_STORE>(p, pl.splits, pl.split_k, s);
-    case EPI_BIAS: return launch<WM, WN, AK, BKC, EPI_BIAS>(p, pl.splits, pl.split_k, s);
-    case EPI_BIAS_RESID: return launch<WM, WN, AK, BKC, EPI_BIAS_RESID>(p, pl.splits, pl.split_k, s);
-    case EPI_BIAS_GELU: return launch<WM, WN, AK, BKC, EPI_BIAS_GELU>(p, pl.splits, pl.split_k, s);
-    case EPI_GELU_BWD: return launch<WM, WN, AK, BKC, EPI_GELU_BWD>(p, pl.splits, pl.split_k, s);
-    case EPI_F32_ACC: return launch<WM, WN, AK, BKC, EPI_F32_ACC>(p, pl.splits, pl.split_k, s);
-    default: return launch<WM, WN, AK, BKC, EPI_F32_STORE>(p, pl.splits, pl.split_k, s);
+    case EPI_STORE: return launch<AK, BKC, EPI_STORE>(p, pl, s);
+    case EPI_BIAS: return launch<AK, BKC, EPI_BIAS>(p, pl, s);
+    case EPI_BIAS_RESID: return launch<AK, BKC, EPI_BIAS_RESID>(p, pl, s);
+    case EPI_BIAS_GELU: return launch<AK, BKC, EPI_BIAS_GELU>(p, pl, s);
+    case EPI_GELU_BWD: return launch<AK, BKC, EPI_GELU_BWD>(p, pl, s);
+    case EPI_F32_ACC: return launch<AK, BKC, EPI_F32_ACC>(p, pl, s);
+    default: return launch<AK, BKC, EPI_F32_STORE>(p, pl, s);
   }
 }
 
 }  // namespace
 
 GemmWork gemm_f32_work(long M, long N, long nseg, long seg) {
-  return {plan_f32(M, N, nseg, seg, GEMM_SPLIT_MAX_FLOATS, 256).split_floats, 0};
+  return {plan_f32(M, N, nseg, seg, 1, GEMM_SPLIT_MAX_FLOATS, 256).split_floats, 0};
 }
 
 hipError_t gemm_f32(const GemmParams& p, hipStream_t s) {
@@ -256,9 +335,9 @@ hipError_t gemm_f32(const GemmParams& p, hipStream_t s) {
   if ((p.a_kcontig ? p.K : p.M) % 4 || (p.b_kcontig ? p.K : p.N) % 4 || p.lda % 4 || p.ldb % 4 ||
       (p.kseg_len > 0 && (p.a_kcontig || p.b_kcontig) && p.kseg_len % 4))
     return hipErrorInvalidValue;
-  if (p.colsum_out != nullptr) return hipErrorInvalidValue;  // bf16 products only
-  if (p.a_kcontig && !p.b_kcontig) return launch_epi<1, 1, true, false>(p, s);
-  if (p.a_kcontig && p.b_kcontig) return launch_epi<1, 1, true, true>(p, s);
-  if (!p.a_kcontig && !p.b_kcontig) return launch_epi<1, 1, false, false>(p, s);
+  if (p.colsum_work != nullptr) return hipErrorInvalidValue;  // bf16 products only
+  if (p.a_kcontig && !p.b_kcontig) return launch_epi<true, false>(p, s);
+  if (p.a_kcontig && p.b_kcontig) return launch_epi<true, true>(p, s);
+  if (!p.a_kcontig && !p.b_kcontig) return launch_epi<false, false>(p, s);
   return hipErrorInvalidValue;
 }

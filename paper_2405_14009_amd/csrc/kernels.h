@@ -17,23 +17,37 @@ hipError_t ln_backward(int elt, const void* dout, const void* x, const float* me
                        const float* rstd, const float* g, const void* resid, void* dx, long rows,
                        int h, hipStream_t s, void* rcopy = nullptr);
 
-// Column reductions over the rows of nseg segments (one per micro-batch) of
-// a [rows, n] matrix with leading dimension ld, into fp32 outputs (overwrite
-// or accumulate); deterministic two-stage sums (64-row partials, then a fixed
-// order).  n % 4 == 0.
-//   bias (ln = false):  db[c] (+)= sum_r dout[r, c]
-//   ln   (ln = true):   dg[c] (+)= sum_r dout[r, c] * (x[r, c] - mean[r]) * rstd[r];  db as above
-// (x has leading dimension n).  part must hold colsum_part_floats(rows, n, nseg) floats.
-constexpr int COLSUM_MAX_SEG = 32;
+// Column sums of one layer's weight pass over the rows of nseg segments (one
+// per micro-batch, in the stash slots slot[0..nseg) of slot_bytes each), into
+// fp32 outputs (overwrite or accumulate), in a fixed order: partial sums over
+// chunks of rows, then their sum.  A job sums a [rows, n] matrix at byte offset
+// dout of each segment's slot from base:
+//   out[c] (+)= sum_r dout[r, c]
+//   ln:   out_g[c] (+)= sum_r dout[r, c] * (x[r, c] - mean[r]) * rstd[r] as well
+// n * element size is a multiple of 16.
+constexpr int COLSUM_MAX_SEG = 32, COLSUM_MAX_JOBS = 6, COLSUM_MAX_FINISH = 12;
 struct ColSegs {
-  const void* dout[COLSUM_MAX_SEG];
-  const void* x[COLSUM_MAX_SEG];
-  const float* mean[COLSUM_MAX_SEG];
-  const float* rstd[COLSUM_MAX_SEG];
+  const char* base;
+  size_t slot_bytes;
+  int slot[COLSUM_MAX_SEG];
 };
-hipError_t colsum(int elt, bool ln, const ColSegs& segs, int nseg, long ld, long rows, int n, float* dg,
-                  float* db, int accumulate, float* part, hipStream_t s);
-long colsum_part_floats(long rows, int n, int nseg);
+struct ColJob {
+  size_t dout, x, mean, rstd;
+  int n, ln;
+  float *out, *out_g;
+};
+// Partial rows that another kernel left: out[c] (+)= the sum of rows
+// src[0..rows)[c].
+struct ColFinish {
+  const float* src;
+  int rows, n;
+  float* out;
+};
+// part (part_floats long) takes the partials; with colsum_floats of it every
+// job shares two launches, with that of the largest job alone they take more.
+hipError_t colsum(int elt, const ColSegs& segs, int nseg, long rows, const ColJob* jobs, int njobs,
+                  const ColFinish* more, int nmore, int accumulate, float* part, long part_floats, hipStream_t s);
+long colsum_floats(int elt, const ColJob* jobs, int njobs, int nseg, long rows);
 
 // Attention softmax over materialised scores, rows of length s, z*s rows.
 //   forward:  P[r, c] = exp(scale S[r, c] - max) / sum  for c <= q (causal) else 0

@@ -80,10 +80,39 @@ struct Layout {
   WLayer w;
   FLayer fl;
   size_t wslot_bytes, fslot_bytes, off_fslots, stash_bytes;
-  size_t off_S, off_dS, off_dO, off_dv, off_check, off_part, off_cswork, off_split, work_bytes;
-  long split_floats, cs_floats;
+  size_t off_S, off_dS, off_dO, off_dv, off_check, off_part, off_cs[4], off_split, work_bytes;
+  long split_floats, part_floats;
+  long cs_floats[4];  // partial bias sums of each linear layer's weight-gradient product ...
+  bool cs_shared;     // ... in one area, used by one product at a time
   uint64_t acct_af, acct_sw;
 };
+
+// The linear layers in the order their products run: weight, bias, and the
+// stash operands X, dY of dW = X^T dY.
+struct Linear {
+  int pid, bpid;
+  size_t WLayer::*X;
+  size_t WLayer::*dY;
+};
+const Linear kLinear[4] = {{RC_P_W_QKV, RC_P_B_QKV, &WLayer::A, &WLayer::dQKV},
+                           {RC_P_W_O, RC_P_B_O, &WLayer::O, &WLayer::dH},
+                           {RC_P_W_1, RC_P_B_1, &WLayer::C, &WLayer::dU},
+                           {RC_P_W_2, RC_P_B_2, &WLayer::G, &WLayer::dY}};
+
+// Column sums of layer l's weight pass outside its products: the LN
+// parameters' gradients, and on the fp32 path also the biases' (grads: the
+// gradient buffers, nullptr for sizes only).
+int reductions(const Layout& y, int l, float* grads, ColJob* jobs) {
+  auto out = [&](int pid) { return grads ? grads + y.p[l][pid].off : nullptr; };
+  const WLayer& w = y.w;
+  int n = 0;
+  jobs[n++] = {w.dA, w.X, w.mu1, w.r1, y.h, 1, out(RC_P_LN1_B), out(RC_P_LN1_G)};
+  jobs[n++] = {w.dC, w.H, w.mu2, w.r2, y.h, 1, out(RC_P_LN2_B), out(RC_P_LN2_G)};
+  if (!y.bf)
+    for (const Linear& q : kLinear)
+      jobs[n++] = {w.*(q.dY), 0, 0, 0, (int)y.p[l][q.bpid].count, 0, out(q.bpid), nullptr};
+  return n;
+}
 
 rc_status make_layout(const rc_stage_config* c, Layout& y) {
   if (!c) return fail(RC_ERR_INVALID_ARG, "null config");
@@ -213,32 +242,45 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
   // taken where they fit) and partial bias sums of the bf16 weight-gradient
   // products (one product at a time).
   const int nw = std::min(y.wslots, (int)GEMM_MAX_SEG);
-  long want_split = 0;
-  y.cs_floats = 0;
-  {
-    auto product = [&](long M, long N, long nseg, long seg, bool wgrad) {
+  long want_split = 0, want_part = 0;
+  const long shapes[4][2] = {{h, 3 * h}, {h, h}, {h, f}, {f, h}};  // [in, out] of the linear layers
+  for (int i = 0; i < 4; ++i) {
+    y.cs_floats[i] = 0;
+    auto product = [&](long M, long N, long nseg, long seg) {
       const GemmWork g = y.bf ? gemm_bf16_work(M, N, nseg, seg) : gemm_f32_work(M, N, nseg, seg);
       want_split = std::max(want_split, g.split_floats);
-      if (wgrad && y.bf) y.cs_floats = std::max(y.cs_floats, g.colsum_floats);
+      return y.bf ? g.colsum_floats : 0L;
     };
-    const long shapes[4][2] = {{h, 3 * h}, {h, h}, {h, f}, {f, h}};  // [in, out] of the linear layers
-    for (auto& q : shapes) {
-      product(y.T, q[1], 1, q[0], false);  // Y = X W
-      product(y.T, q[0], 1, q[1], false);  // dX = dY W^T
-      for (int n = 1; n <= nw; ++n) product(q[0], q[1], n, y.T, true);  // dW = X^T dY of n micro-batches
-    }
+    const long in = shapes[i][0], out = shapes[i][1];
+    product(y.T, out, 1, in);  // Y = X W
+    product(y.T, in, 1, out);  // dX = dY W^T
+    for (int n = 1; n <= nw; ++n)  // dW = X^T dY of n micro-batches
+      y.cs_floats[i] = std::max(y.cs_floats[i], product(in, out, n, y.T));
   }
-  // RC_STATIC_WORK_BYTES admits a configuration by what it needs without
-  // partials of split reductions, counted as part and cs below; those partials
-  // take the rest of that memory at most.
-  const size_t part = 4 * colsum_part_floats(y.T, (int)std::max(3 * h, f), nw);
+  ColJob jobs[COLSUM_MAX_JOBS];
+  const int njobs = reductions(y, 0, nullptr, jobs);
+  for (int n = 1; n <= nw; ++n) want_part = std::max(want_part, colsum_floats(y.elt, jobs, njobs, n, y.T));
+  // RC_STATIC_WORK_BYTES admits a configuration by what it needs with one
+  // column sum at a time (64 rows a partial) and bias sums over 256-row tiles,
+  // without partials of split reductions; what goes beyond that takes the rest
+  // of that memory at most.
+  const long chunks = nw * ((y.T + 63) / 64);
+  const size_t part = 8 * (chunks + (chunks + 15) / 16) * std::max(3 * h, f);
   const size_t cs = y.bf ? 4 * std::max((h + 255) / 256 * std::max(3 * h, f), (f + 255) / 256 * h) : 0;
   const size_t need = align_up(o + part) + align_up(cs);
-  // bf16 stages reduce only h columns outside the products
-  y.off_part = take(y.bf ? 4 * colsum_part_floats(y.T, (int)h, nw) : part);
-  if (need <= RC_STATIC_WORK_BYTES && o + 4 * y.cs_floats > RC_STATIC_WORK_BYTES)
-    y.cs_floats = (long)(need - o) / 4;  // at least cs
-  y.off_cswork = take(4 * y.cs_floats);
+  auto bias_floats = [&] { return y.cs_floats[0] + y.cs_floats[1] + y.cs_floats[2] + y.cs_floats[3]; };
+  auto over = [&](long cs_bytes) {
+    return need <= RC_STATIC_WORK_BYTES && o + 4 * want_part + cs_bytes + 5 * kAlign > RC_STATIC_WORK_BYTES;
+  };
+  if (over(4 * bias_floats())) {
+    for (int i = 0; i < 4; ++i) y.cs_floats[i] = y.bf ? (shapes[i][0] + 255) / 256 * shapes[i][1] : 0;
+    want_part = std::min<long>(want_part, y.bf ? 2 * chunks * h : 2 * chunks * std::max(3 * h, f));
+  }
+  y.cs_shared = over(4 * bias_floats());
+  y.part_floats = want_part;
+  y.off_part = take(4 * want_part);
+  for (int i = 0; i < 4; ++i) y.off_cs[i] = y.cs_shared ? o : take(4 * y.cs_floats[i]);
+  if (y.cs_shared) take(4 * *std::max_element(y.cs_floats, y.cs_floats + 4));
   y.off_split = o;
   size_t total = std::max(need, align_up(o + 4 * want_split));
   if (need <= RC_STATIC_WORK_BYTES) total = std::min(total, (size_t)RC_STATIC_WORK_BYTES);
@@ -530,8 +572,12 @@ rc_status run_backward_input(rc_stage* st, int ws, int fs, const void* dy, void*
     FPtr fl = fptr(st, fs, l);
     // The last layer reads the caller's dy; its LN2 backward, which adds dy as
     // the residual, also copies it into the stash for the weight pass.
+    // (The products copy 16 bytes at a time; a dy that is not aligned to that is
+    // copied first.)
     const bool top = l == L - 1;
-    char* const dYl = top ? (char*)dy : w.dY;
+    const bool direct = top && (uintptr_t)dy % 16 == 0;
+    if (top && !direct) HIPCHK(hipMemcpyAsync(w.dY, dy, T * h * E, hipMemcpyDeviceToDevice, s));
+    char* const dYl = direct ? (char*)dy : w.dY;
     // dU = (dY W_2^T) * gelu'(U), the derivative stored by the forward
     GemmParams g = gp(T, f, h, dYl, h, 1, weight(st, l, RC_P_W_2), h, 1, EPI_GELU_BWD, w.dU, f);
     g.aux = fl.Dg;
@@ -544,7 +590,7 @@ rc_status run_backward_input(rc_stage* st, int ws, int fs, const void* dy, void*
     {
       Prof pr(st, RC_K_LN, 0, ln_b_bytes + (top ? (double)T * h * E : 0.0));
       HIPCHK(ln_backward(E, w.dC, w.H, w.mu2, w.r2, master(st, l, RC_P_LN2_G), dYl, w.dH, T, y.h, s,
-                         top ? w.dY : nullptr));
+                         direct ? w.dY : nullptr));
     }
     // dO = dH W_o^T
     g = gp(T, h, h, w.dH, h, 1, weight(st, l, RC_P_W_O), h, 1, EPI_STORE, dO, h);
@@ -575,75 +621,51 @@ rc_status run_backward_weight(rc_stage* st, const int* ws, int n) {
   const int acc = st->grads_fresh ? 0 : 1;
   hipStream_t s = st->stream;
   float* part = (float*)(st->work + y.off_part);
+  float* grads = (float*)(st->state + y.off_grad);
   for (int l = 0; l < y.L; ++l) {
-    WPtr w[GEMM_MAX_SEG];
-    for (int q = 0; q < n; ++q) w[q] = wptr(st, ws[q], l);
-    // pid: the weight; bpid: the bias of the same linear layer, whose gradient
-    // sum_t dY[t, :] the bf16 weight-gradient product computes on the side
-    // from the dY tiles it stages (the fp32 path leaves it to the column sums).
-    struct {
-      int pid, bpid;
-      long M, N;
-      char* WPtr::*X;
-      char* WPtr::*dY;
-    } lin[4] = {{RC_P_W_QKV, RC_P_B_QKV, h, 3 * h, &WPtr::A, &WPtr::dQKV},
-                {RC_P_W_O, RC_P_B_O, h, h, &WPtr::O, &WPtr::dH},
-                {RC_P_W_1, RC_P_B_1, h, f, &WPtr::C, &WPtr::dU},
-                {RC_P_W_2, RC_P_B_2, f, h, &WPtr::G, &WPtr::dY}};
-    for (auto& q : lin) {
-      // dW (+)= sum over the n micro-batches of X^T dY (reduction over tokens)
-      GemmParams g = gp(q.M, q.N, T * n, nullptr, q.M, 0, nullptr, q.N, 0, EPI_F32_ACC,
-                        gradp(st, l, q.pid), q.N);
+    ColSegs sg;
+    sg.base = st->stash + (size_t)l * y.w.bytes;
+    sg.slot_bytes = y.wslot_bytes;
+    for (int k = 0; k < n; ++k) sg.slot[k] = ws[k];
+    // dW (+)= sum over the n micro-batches of X^T dY (reduction over tokens).
+    // The bias gradient sum_t dY[t, :] of a bf16 stage comes from the dY tiles
+    // the product stages: partial rows that the layer's column sums add up
+    // (the fp32 path leaves all of it to them).
+    ColFinish bias[4];
+    int nbias = 0;
+    for (int i = 0; i < 4; ++i) {
+      const Linear& q = kLinear[i];
+      const long M = i == 3 ? f : h, N = y.p[l][q.bpid].count;
+      GemmParams g = gp(M, N, T * n, nullptr, M, 0, nullptr, N, 0, EPI_F32_ACC, gradp(st, l, q.pid), N);
       g.accumulate = acc;
+      int rows = 0;
       if (y.bf) {
-        g.colsum_out = gradp(st, l, q.bpid);
-        g.colsum_acc = acc;
-        g.colsum_work = (float*)(st->work + y.off_cswork);
-        g.colsum_floats = y.cs_floats;
+        g.colsum_work = (float*)(st->work + y.off_cs[i]);
+        g.colsum_floats = y.cs_floats[i];
+        g.colsum_rows = &rows;
       }
       g.kseg_len = (int)T;
       for (int k = 0; k < n; ++k) {
-        g.segA[k] = w[k].*(q.X);
-        g.segB[k] = w[k].*(q.dY);
+        const char* slot = sg.base + ws[k] * y.wslot_bytes;
+        g.segA[k] = slot + y.w.*(q.X);
+        g.segB[k] = slot + y.w.*(q.dY);
       }
       HIPCHK(gemm_lin(st, g, RC_K_GEMM_WGRAD));
+      if (!y.bf) continue;
+      bias[nbias++] = {g.colsum_work, rows, (int)N, gradp(st, l, q.bpid)};
+      if (y.cs_shared) {
+        HIPCHK(colsum(E, sg, n, T, nullptr, 0, bias, nbias, acc, nullptr, 0, s));
+        nbias = 0;
+      }
     }
-    // Column sums: the LN parameters' gradients, and on the fp32 path also the
-    // biases' (bytes: n micro-batches' inputs, then the gradient update).
+    // Column sums (bytes: n micro-batches' inputs, then the gradient update).
     const double rb = acc ? 8.0 : 4.0;
     const double bias_in = y.bf ? 0.0 : (double)T * (6 * h + f) * E;
     Prof pr(st, RC_K_REDUCE, 0,
             n * (bias_in + 4.0 * T * h * E + 16.0 * T) + (y.bf ? 0.0 : rb * (6 * h + f)) + 4 * rb * h);
-    ColSegs sg;
-    std::memset(&sg, 0, sizeof(sg));
-    struct {
-      int pid;
-      long N;
-      char* WPtr::*D;
-    } bias[4] = {{RC_P_B_QKV, 3 * h, &WPtr::dQKV}, {RC_P_B_O, h, &WPtr::dH},
-                 {RC_P_B_1, f, &WPtr::dU}, {RC_P_B_2, h, &WPtr::dY}};
-    if (!y.bf) {
-      for (auto& b : bias) {
-        for (int k = 0; k < n; ++k) sg.dout[k] = w[k].*(b.D);
-        HIPCHK(colsum(E, false, sg, n, b.N, T, (int)b.N, nullptr, gradp(st, l, b.pid), acc, part, s));
-      }
-    }
-    for (int k = 0; k < n; ++k) {
-      sg.dout[k] = w[k].dA;
-      sg.x[k] = w[k].X;
-      sg.mean[k] = w[k].mu1;
-      sg.rstd[k] = w[k].r1;
-    }
-    HIPCHK(colsum(E, true, sg, n, h, T, (int)h, gradp(st, l, RC_P_LN1_G), gradp(st, l, RC_P_LN1_B), acc,
-                  part, s));
-    for (int k = 0; k < n; ++k) {
-      sg.dout[k] = w[k].dC;
-      sg.x[k] = w[k].H;
-      sg.mean[k] = w[k].mu2;
-      sg.rstd[k] = w[k].r2;
-    }
-    HIPCHK(colsum(E, true, sg, n, h, T, (int)h, gradp(st, l, RC_P_LN2_G), gradp(st, l, RC_P_LN2_B), acc,
-                  part, s));
+    ColJob jobs[COLSUM_MAX_JOBS];
+    const int njobs = reductions(y, l, grads, jobs);
+    HIPCHK(colsum(E, sg, n, T, jobs, njobs, bias, nbias, acc, part, y.part_floats, s));
   }
   return RC_OK;
 }
