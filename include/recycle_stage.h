@@ -278,8 +278,10 @@ rc_status rc_stage_op_log(rc_stage* st, rc_op_record* buf, int32_t cap, int32_t*
  * Read as: F +a_f, B_input +(s_w - a_f), B_weight -s_w, coupled backward
  * -a_f.  Byte counts are the logical sizes of the kept tensors (no alignment
  * padding), per micro-batch over all layers:
- *   a_f = L (E (8 T h + 2 T f) + 16 T + attn),  attn = 4 b heads s (fused
- *         attention's row statistics) or E b heads s^2 (probabilities);
+ *   a_f = L (E (8 T h + 2 T f) + 16 T + attn),  attn = 4 b heads s (bf16 stages
+ *         of head_dim 128: fused attention's row statistics) or E b heads s^2
+ *         (probabilities; counted for every other stage, also where fused
+ *         attention keeps less, so that a limit means the same for all);
  *   s_w = L (E (12 T h + 2 T f) + 16 T);   E = element bytes, T = b s. */
 typedef struct rc_stash_account {
   uint64_t a_f;    /* bytes a micro-batch holds from its F to its B_input */
@@ -348,12 +350,16 @@ rc_status rc_stage_profile_read(rc_stage* st, rc_kernel_stat* out);
 /* Attention kernels the handle's F and B_input run (chosen from the shape
  * and the compute-unit count of the current device):
  *   RC_ATTN_MATERIALISED  scores and probabilities in memory, GEMM + softmax
- *                         kernels (fp32 stages, head_dim != 128);
+ *                         kernels (fp32 stages, head_dim > 128, and other
+ *                         head_dim != 128 at seq_len <= 128);
  *   RC_ATTN_BLOCK         fused online softmax, one workgroup per block of
  *                         128 queries (non-causal, or causal grids that would
  *                         fill the last round of paired workgroups poorly);
  *   RC_ATTN_PAIRED        fused causal, one workgroup per pair of query
  *                         blocks (q, last - q) of equal total length.
+ * (Grids of at most one workgroup of 32 queries per compute unit, two for
+ * head_dim <= 64, run the fused kernels' form for small grids, whose waves
+ * share a block's keys, under either of the two names.)
  * Host only; works on dry-run handles.  Errors: RC_ERR_INVALID_ARG. */
 enum { RC_ATTN_MATERIALISED = 0, RC_ATTN_BLOCK = 1, RC_ATTN_PAIRED = 2 };
 rc_status rc_stage_attention_kernels(rc_stage* st, int32_t* kind);

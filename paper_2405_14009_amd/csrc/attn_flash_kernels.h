@@ -605,6 +605,64 @@ static __device__ __forceinline__ void attn_fwd_pair(const AttnArgs& p) {
   }
 }
 
+// One query block (queries qs..qs+63; tiles and row vectors at st) for the wave's
+// keys k0w..k0w+31 (this lane's key).
+template <bool CAUSAL>
+static __device__ __forceinline__ void bwdkv_block(f32x16 (&dk)[HD / 32], f32x16 (&dv)[HD / 32],
+                                                   const bf16x8 (&kf)[HD / 16], const bf16x8 (&vf)[HD / 16],
+                                                   const char* st, const RowOffs& ro, const TrOffs& to, int qs,
+                                                   int k0w, int key, int lane, const AttnArgs& p) {
+  if (CAUSAL && qs + 63 < k0w) return;  // every query of the block precedes every key of the wave
+  const char* qt = st;
+  const char* ot = st + TILE64;
+  const float* lse = (const float*)(st + 2 * TILE64);
+  const float* dvv = (const float*)(st + 2 * TILE64 + 1024);
+  const bool need_mask = uniform(CAUSAL && qs < k0w + 31);
+  // the two 32-query halves of the block in turn (one half's scores live)
+#pragma unroll 1
+  for (int j = 0; j < 2; ++j) {
+    f32x16 sc, dp;
+    zero(sc);
+    zero(dp);
+    two_chains<2>(sc, qt, j, kf, dp, ot, j, vf, ro);
+    float Dv[16];
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg) {
+      const int ql = 32 * j + 8 * rg + 4 * (lane >> 5);
+      const float4 L4 = *(const float4*)(lse + ql);
+      const float4 D4 = *(const float4*)(dvv + ql);
+      const float Lv[4] = {L4.x, L4.y, L4.z, L4.w};
+      Dv[4 * rg] = D4.x;
+      Dv[4 * rg + 1] = D4.y;
+      Dv[4 * rg + 2] = D4.z;
+      Dv[4 * rg + 3] = D4.w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sc[4 * rg + e] = __builtin_amdgcn_exp2f(sc[4 * rg + e] * p.sl2 - Lv[e]);
+    }
+    // element r holds query qs + 32 j + 4 (l / 32) + kofs(r): masked when
+    // that query precedes this lane's key
+    if (need_mask) {
+      const int room = key - qs - 32 * j - 4 * (lane >> 5);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (kofs(r) < room) sc[r] = 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dp[r] = sc[r] * (dp[r] - Dv[r]);
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      const int t = 2 * j + hf;
+      const bf16x8 pf = pack_half(sc, hf);
+      const bf16x8 sf = pack_half(dp, hf);
+#pragma unroll
+      for (int b = 0; b < HD / 32; ++b) {
+        dv[b] = mfma(rd_tr(ot, to, b, t), pf, dv[b]);
+        dk[b] = mfma(rd_tr(qt, to, b, t), sf, dk[b]);
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Backward over key blocks: dK, dV.  Workgroup: 128 keys of one (sequence,
 // head), 4 waves x 32 keys (K and V rows stationary in registers); query
@@ -658,56 +716,7 @@ static __device__ __forceinline__ void attn_bwd_kv(const AttnArgs& p) {
     if (wave == 1) load_vec64(rd, st + 2 * TILE64 + 1024, lane, qb * 64, p.s);
   };
   auto compute = [&](const char* st, int qb) {
-    const int qs = qb * 64;
-    if (CAUSAL && qs + 63 < k0w) return;  // every query of the block precedes every key of the wave
-    const char* qt = st;
-    const char* ot = st + TILE64;
-    const float* lse = (const float*)(st + 2 * TILE64);
-    const float* dvv = (const float*)(st + 2 * TILE64 + 1024);
-    const bool need_mask = uniform(CAUSAL && qs < k0w + 31);
-    // the two 32-query halves of the block in turn (one half's scores live)
-#pragma unroll 1
-    for (int j = 0; j < 2; ++j) {
-      f32x16 sc, dp;
-      zero(sc);
-      zero(dp);
-      two_chains<2>(sc, qt, j, kf, dp, ot, j, vf, ro);
-      float Dv[16];
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int ql = 32 * j + 8 * rg + 4 * (lane >> 5);
-        const float4 L4 = *(const float4*)(lse + ql);
-        const float4 D4 = *(const float4*)(dvv + ql);
-        const float Lv[4] = {L4.x, L4.y, L4.z, L4.w};
-        Dv[4 * rg] = D4.x;
-        Dv[4 * rg + 1] = D4.y;
-        Dv[4 * rg + 2] = D4.z;
-        Dv[4 * rg + 3] = D4.w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sc[4 * rg + e] = __builtin_amdgcn_exp2f(sc[4 * rg + e] * p.sl2 - Lv[e]);
-      }
-      // element r holds query qs + 32 j + 4 (l / 32) + kofs(r): masked when
-      // that query precedes this lane's key
-      if (need_mask) {
-        const int room = key - qs - 32 * j - 4 * (lane >> 5);
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (kofs(r) < room) sc[r] = 0.f;
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dp[r] = sc[r] * (dp[r] - Dv[r]);
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        const int t = 2 * j + hf;
-        const bf16x8 pf = pack_half(sc, hf);
-        const bf16x8 sf = pack_half(dp, hf);
-#pragma unroll
-        for (int b = 0; b < HD / 32; ++b) {
-          dv[b] = mfma(rd_tr(ot, to, b, t), pf, dv[b]);
-          dk[b] = mfma(rd_tr(qt, to, b, t), sf, dk[b]);
-        }
-      }
-    }
+    bwdkv_block<CAUSAL>(dk, dv, kf, vf, st, ro, to, qb * 64, k0w, key, lane, p);
   };
 
   const int n = nqb_all - qb0;
@@ -989,6 +998,269 @@ static __device__ __forceinline__ void attn_bwd_q_pair(const AttnArgs& p) {
     store_dq(dq, p, z, q0, qq, lane, lds + FWD_GROUP + wg * 32 * RS);
   }
 }
+
+// ---------------------------------------------------------------------------
+// Small grids.  With at most one workgroup of 32 rows per compute unit the
+// kernels above leave most of the chip idle, and their time is the chain of
+// 64-row blocks that one workgroup walks (s = 512, 16 heads of 64: 32
+// workgroups of up to ten steps, 14.6 us forward).  Here a workgroup takes 32
+// queries (or keys), and its four waves walk every fourth block of the other
+// side each, with tiles of their own: no barrier until the four partial states
+// are combined through LDS in wave order.
+static constexpr int SPLIT_TILE = 2 * TILE64 + 2048;  // a wave's two tiles (and two row vectors)
+
+// This wave's copies have landed; its LDS reads stay behind (no other wave
+// reads its tiles, so no barrier is needed).
+static __device__ __forceinline__ void own_copies_landed() {
+  __builtin_amdgcn_sched_barrier(0);
+  vm_drain();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// This wave's LDS reads are complete: its tiles may be overwritten.
+static __device__ __forceinline__ void own_reads_done() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// The wave's own copy of a 64-row tile.
+static __device__ __forceinline__ void load_tile_own(const i32x4& rs, char* tile, int lane, long ld, int row0,
+                                                     int nrows, int d) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) load_tile<64>(rs, tile, v, lane, ld, row0, nrows, d);
+}
+
+// This wave's accumulators into its merge area / one 32-column block of wave
+// u's back (float4 chunks [block][4][lane]).
+template <int NB>
+static __device__ __forceinline__ void put_acc(const f32x16 (&a)[NB], char* area, int first, int lane) {
+  float4* dst = (float4*)area + lane;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      dst[(4 * (first + b) + c) * 64] = make_float4(a[b][4 * c], a[b][4 * c + 1], a[b][4 * c + 2], a[b][4 * c + 3]);
+}
+static __device__ __forceinline__ void get_acc(f32x16& a, const char* area, int b, int lane) {
+  const float4* src = (const float4*)area + lane;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float4 v = src[(4 * b + c) * 64];
+    a[4 * c] = v.x;
+    a[4 * c + 1] = v.y;
+    a[4 * c + 2] = v.z;
+    a[4 * c + 3] = v.w;
+  }
+}
+// 32 columns (block b) of the 32 rows from row0, lane column = row.
+static __device__ __forceinline__ void store_block(const f32x16& a, bf16* base, long ld, int row, int nrows, int b,
+                                                   int lane, float mul, int d) {
+  if (row >= nrows) return;
+  bf16* p = base + (long)row * ld + 32 * b + 4 * (lane >> 5);
+#pragma unroll
+  for (int rg = 0; rg < 4; ++rg) {
+    bf16 t[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = (bf16)(a[4 * rg + e] * mul);
+    if (FULL || 32 * b + 8 * rg < d) *(uint2*)(p + 8 * rg) = *(const uint2*)t;
+  }
+}
+
+template <bool CAUSAL>
+static __device__ __forceinline__ void attn_fwd_split(const AttnArgs& p) {
+  __shared__ __attribute__((aligned(1024))) char lds[4 * SPLIT_TILE];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* const area = lds + wave * SPLIT_TILE;
+  const int z = blockIdx.x % p.bh, blk = blockIdx.x / p.bh;
+  const int zb = z / p.heads, zh = z % p.heads;
+  const long ld = 3L * p.h;
+  const bf16* Q = p.qkv + (long)zb * p.s * ld + zh * dim(p);
+  const i32x4 rk = make_rsrc(Q + p.h, 2L * p.s * ld);
+  const i32x4 rv = make_rsrc(Q + 2 * p.h, 2L * p.s * ld);
+  const int q0 = blk * 32, qq = q0 + (lane & 31);
+  const int nkb_all = (p.s + 63) / 64;
+  const int nkb = CAUSAL ? min(nkb_all, (q0 + 31) / 64 + 1) : nkb_all;
+  auto issue = [&](int kb) {
+    load_tile_own(rk, area, lane, ld, kb * 64, p.s, dim(p));
+    load_tile_own(rv, area + TILE64, lane, ld, kb * 64, p.s, dim(p));
+  };
+  if (wave < nkb) issue(wave);
+  bf16x8 qf[HD / 16];
+  load_stationary(qf, Q, ld, qq, p.s, lane, dim(p));
+  RowOffs ro;
+  ro.init(lane);
+  TrOffs to;
+  to.init(lane);
+  FwdState st;
+  st.reset();
+  for (int kb = wave; kb < nkb; kb += 4) {
+    own_copies_landed();
+    fwd_block<CAUSAL>(st, qf, area, area + TILE64, ro, to, kb * 64, q0, qq, lane, p);
+    if (kb + 4 < nkb) {
+      own_reads_done();
+      issue(kb + 4);
+    }
+  }
+  own_reads_done();
+  put_acc<HD / 32>(st.o, area, 0, lane);
+  float2* const stat = (float2*)(area + 2 * TILE64);
+  stat[lane] = make_float2(st.m_run, st.l_run + __shfl_xor(st.l_run, 32, 64));
+  __syncthreads();
+  float2 ml[4];
+  float m = -1e30f, l = 0.f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    ml[u] = ((const float2*)(lds + u * SPLIT_TILE + 2 * TILE64))[lane];
+    m = fmaxf(m, ml[u].x);
+  }
+  float a[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    a[u] = __builtin_amdgcn_exp2f(ml[u].x - m);
+    l += a[u] * ml[u].y;
+  }
+  bf16* const out = (bf16*)p.out + (long)zb * p.s * p.h + zh * dim(p);
+  for (int b = wave; b < HD / 32; b += 4) {
+    f32x16 o;
+    zero(o);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      f32x16 w;
+      get_acc(w, lds + u * SPLIT_TILE, b, lane);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[r] += w[r] * a[u];
+    }
+    store_block(o, out, p.h, qq, p.s, b, lane, 1.0f / l, dim(p));
+  }
+  if (wave == 0 && lane < 32 && qq < p.s) p.lse[(long)z * p.s + qq] = m + __builtin_amdgcn_logf(l);
+}
+
+template <bool CAUSAL>
+static __device__ __forceinline__ void attn_bwd_q_split(const AttnArgs& p) {
+  __shared__ __attribute__((aligned(1024))) char lds[4 * SPLIT_TILE];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* const area = lds + wave * SPLIT_TILE;
+  const int z = blockIdx.x % p.bh, blk = blockIdx.x / p.bh;
+  const int zb = z / p.heads, zh = z % p.heads;
+  const long ld = 3L * p.h;
+  const bf16* Q = p.qkv + (long)zb * p.s * ld + zh * dim(p);
+  const i32x4 rk = make_rsrc(Q + p.h, 2L * p.s * ld);
+  const i32x4 rv = make_rsrc(Q + 2 * p.h, 2L * p.s * ld);
+  const int q0 = blk * 32, qq = q0 + (lane & 31);
+  const int nkb_all = (p.s + 63) / 64;
+  const int nkb = CAUSAL ? min(nkb_all, (q0 + 31) / 64 + 1) : nkb_all;
+  auto issue = [&](int kb) {
+    load_tile_own(rk, area, lane, ld, kb * 64, p.s, dim(p));
+    load_tile_own(rv, area + TILE64, lane, ld, kb * 64, p.s, dim(p));
+  };
+  if (wave < nkb) issue(wave);
+  BwdQRows w;
+  w.load(p, z, qq, lane, wave == 0);
+  RowOffs ro;
+  ro.init(lane);
+  TrOffs to;
+  to.init(lane);
+  f32x16 dq[HD / 32];
+#pragma unroll
+  for (int b = 0; b < HD / 32; ++b) zero(dq[b]);
+  for (int kb = wave; kb < nkb; kb += 4) {
+    own_copies_landed();
+    bwdq_block<CAUSAL>(dq, w, area, area + TILE64, ro, to, kb * 64, q0, qq, lane, p);
+    if (kb + 4 < nkb) {
+      own_reads_done();
+      issue(kb + 4);
+    }
+  }
+  own_reads_done();
+  put_acc<HD / 32>(dq, area, 0, lane);
+  __syncthreads();
+  bf16* const out = (bf16*)p.out + (long)zb * p.s * ld + zh * dim(p);
+  for (int b = wave; b < HD / 32; b += 4) {
+    f32x16 o;
+    get_acc(o, lds, b, lane);
+#pragma unroll
+    for (int u = 1; u < 4; ++u) {
+      f32x16 t;
+      get_acc(t, lds + u * SPLIT_TILE, b, lane);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[r] += t[r];
+    }
+    store_block(o, out, ld, qq, p.s, b, lane, p.scale, dim(p));
+  }
+}
+
+template <bool CAUSAL>
+static __device__ __forceinline__ void attn_bwd_kv_split(const AttnArgs& p) {
+  __shared__ __attribute__((aligned(1024))) char lds[4 * SPLIT_TILE];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* const area = lds + wave * SPLIT_TILE;
+  const int z = blockIdx.x % p.bh, blk = blockIdx.x / p.bh;
+  const int zb = z / p.heads, zh = z % p.heads;
+  const long ld = 3L * p.h;
+  const bf16* Q = p.qkv + (long)zb * p.s * ld + zh * dim(p);
+  const bf16* dO = p.dout + (long)zb * p.s * p.h + zh * dim(p);
+  const i32x4 rq = make_rsrc(Q, 2L * p.s * ld);
+  const i32x4 rdo = make_rsrc(dO, 2L * p.s * p.h);
+  const i32x4 rl = make_rsrc(p.lse + (long)z * p.s, 4L * p.s);
+  const i32x4 rd = make_rsrc(p.dv + (long)z * p.s, 4L * p.s);
+  const int k0w = blk * 32, key = k0w + (lane & 31);
+  const int nqb = (p.s + 63) / 64;
+  const int first = (CAUSAL ? k0w / 64 : 0) + wave;
+  auto issue = [&](int qb) {
+    load_tile_own(rq, area, lane, ld, qb * 64, p.s, dim(p));
+    load_tile_own(rdo, area + TILE64, lane, p.h, qb * 64, p.s, dim(p));
+    load_vec64(rl, area + 2 * TILE64, lane, qb * 64, p.s);
+    load_vec64(rd, area + 2 * TILE64 + 1024, lane, qb * 64, p.s);
+  };
+  if (first < nqb) issue(first);
+  bf16x8 kf[HD / 16], vf[HD / 16];
+  load_stationary(kf, Q + p.h, ld, key, p.s, lane, dim(p));
+  load_stationary(vf, Q + 2 * p.h, ld, key, p.s, lane, dim(p));
+  RowOffs ro;
+  ro.init(lane);
+  TrOffs to;
+  to.init(lane);
+  f32x16 dk[HD / 32], dv[HD / 32];
+#pragma unroll
+  for (int b = 0; b < HD / 32; ++b) {
+    zero(dk[b]);
+    zero(dv[b]);
+  }
+  for (int qb = first; qb < nqb; qb += 4) {
+    own_copies_landed();
+    bwdkv_block<CAUSAL>(dk, dv, kf, vf, area, ro, to, qb * 64, k0w, key, lane, p);
+    if (qb + 4 < nqb) {
+      own_reads_done();
+      issue(qb + 4);
+    }
+  }
+  own_reads_done();
+  put_acc<HD / 32>(dk, area, 0, lane);
+  put_acc<HD / 32>(dv, area, HD / 32, lane);
+  __syncthreads();
+  bf16* const out = p.out + (long)zb * p.s * ld + p.h + zh * dim(p);
+  for (int b = wave; b < 2 * (HD / 32); b += 4) {
+    f32x16 o;
+    get_acc(o, lds, b, lane);
+#pragma unroll
+    for (int u = 1; u < 4; ++u) {
+      f32x16 t;
+      get_acc(t, lds + u * SPLIT_TILE, b, lane);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[r] += t[r];
+    }
+    const bool isv = b >= HD / 32;
+    store_block(o, isv ? out + p.h : out, ld, key, p.s, isv ? b - HD / 32 : b, lane, isv ? 1.0f : p.scale, dim(p));
+  }
+}
+// put_acc of dk and dv: 2 (HD / 32) blocks of 4 KB in the two tiles
+static_assert(2 * (HD / 32) * 4096 <= 2 * TILE64, "merge area");
+
 };
 
 // Kernels.  The 128-column ones hold two waves per SIMD in registers; the
@@ -1014,11 +1286,40 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, HD > 64 
   Attn<HD, FULL>::attn_bwd_q_pair(p);
 }
 
+template <int HD, bool FULL, bool CAUSAL>
+__global__ __launch_bounds__(256) void attn_fwd_split_k(AttnArgs p) {
+  Attn<HD, FULL>::template attn_fwd_split<CAUSAL>(p);
+}
+template <int HD, bool FULL, bool CAUSAL>
+__global__ __launch_bounds__(256) void attn_bwd_q_split_k(AttnArgs p) {
+  Attn<HD, FULL>::template attn_bwd_q_split<CAUSAL>(p);
+}
+template <int HD, bool FULL, bool CAUSAL>
+__global__ __launch_bounds__(256) void attn_bwd_kv_split_k(AttnArgs p) {
+  Attn<HD, FULL>::template attn_bwd_kv_split<CAUSAL>(p);
+}
+
+// Whether the launch takes the kernels of small grids: no more workgroups of
+// 32 rows than compute units hold at once (the tiles of a head of up to 64
+// columns let two share a CU).
+template <int HD>
+bool split_grid(const AttnArgs& a) {
+  return (long)((a.s + 31) / 32) * a.bh <= (HD <= 64 ? 2L : 1L) * device_compute_units();
+}
+
 template <int HD, bool FULL>
 hipError_t attn_fwd_launch(const AttnArgs& a, int causal, bool paired, hipStream_t st) {
   const int nqb = (a.s + 127) / 128;
   const long pairs = (long)((nqb + 1) / 2) * a.bh;
   const dim3 grid((unsigned)(nqb * (long)a.bh));
+  if (split_grid<HD>(a)) {
+    const dim3 g((unsigned)(((a.s + 31) / 32) * (long)a.bh));
+    if (causal)
+      hipLaunchKernelGGL((attn_fwd_split_k<HD, FULL, true>), g, dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL((attn_fwd_split_k<HD, FULL, false>), g, dim3(256), 0, st, a);
+    return hipGetLastError();
+  }
   if (causal && paired)
     hipLaunchKernelGGL((attn_fwd_pair_k<HD, FULL>), dim3((unsigned)pairs), dim3(512), 0, st, a);
   else if (causal)
@@ -1034,6 +1335,17 @@ hipError_t attn_bwd_launch(const AttnArgs& a, int causal, bool paired, hipStream
   const int nqb = (a.s + 127) / 128;
   const long pairs = (long)((nqb + 1) / 2) * a.bh;
   const dim3 grid((unsigned)(nqb * (long)a.bh));
+  if (split_grid<HD>(a)) {
+    const dim3 g((unsigned)(((a.s + 31) / 32) * (long)a.bh));
+    if (causal) {
+      hipLaunchKernelGGL((attn_bwd_q_split_k<HD, FULL, true>), g, dim3(256), 0, st, a);
+      hipLaunchKernelGGL((attn_bwd_kv_split_k<HD, FULL, true>), g, dim3(256), 0, st, a);
+    } else {
+      hipLaunchKernelGGL((attn_bwd_q_split_k<HD, FULL, false>), g, dim3(256), 0, st, a);
+      hipLaunchKernelGGL((attn_bwd_kv_split_k<HD, FULL, false>), g, dim3(256), 0, st, a);
+    }
+    return hipGetLastError();
+  }
   if (causal && paired)
     hipLaunchKernelGGL((attn_bwd_q_pair_k<HD, FULL>), dim3((unsigned)pairs), dim3(512), 0, st, a);
   else if (causal)

@@ -38,7 +38,9 @@ def check(cfg, t):
 def test_attention_head_widths(d, seq, causal):
     """Head dimensions below 128, with as many columns as a kernel is compiled
     for and fewer; ragged last query and key blocks; d = 64 at s = 128 takes
-    the materialised kernels."""
+    the materialised kernels.  These grids are small: the kernels that split a
+    block's keys (or queries) over four waves, with one to four of them idle at
+    the shortest sequences."""
     cfg = get_config("small_bf16").with_(layers=1, hidden=4 * d, heads=4, ffn=16 * d, seq=seq, n_mb=2,
                                          rerouted=(1,), causal=causal)
     check(cfg, 2e-2)
@@ -52,6 +54,15 @@ def test_attention_head_widths_per_block(d):
     cfg = get_config("block_bf16").with_(hidden=10 * d, ffn=20 * d, seq=1000, n_mb=1, rerouted=())
     stage = Stage.from_config(cfg, dry_run=True)
     assert stage.attention_kernels() == "block"
+    check(cfg, 2e-2)
+
+
+@pytest.mark.parametrize("d,causal", [(32, True), (64, True), (64, False), (80, True), (80, False), (120, True)])
+def test_attention_head_widths_paired_and_block(d, causal):
+    """Narrow heads on grids of more 32-row workgroups than compute units hold:
+    the kernels of one workgroup per pair (causal) or block of queries."""
+    cfg = get_config("small_bf16").with_(layers=1, hidden=4 * d, heads=4, ffn=8 * d, seq=1128, micro_batch=4, n_mb=1,
+                                         rerouted=(), causal=causal)
     check(cfg, 2e-2)
 
 
