@@ -87,7 +87,7 @@ hipError_t gemm_bf16(const GemmParams& p, hipStream_t s);
 struct GemmWork {
   long split_floats, colsum_floats;
 };
-GemmWork gemm_bf16_work(long M, long N, long nseg, long seg);
+GemmWork gemm_bf16_work(long M, long N, long nseg, long seg, bool tn);  // tn: A and B m/n-contiguous
 GemmWork gemm_f32_work(long M, long N, long nseg, long seg);
 constexpr long GEMM_SPLIT_MAX_FLOATS = 16L << 20;  // most partials of one product
 hipError_t gemm_f32(const GemmParams& p, hipStream_t s);

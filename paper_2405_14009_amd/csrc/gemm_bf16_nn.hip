@@ -30,10 +30,10 @@ hipError_t gemm_bf16(const GemmParams& p, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-GemmWork gemm_bf16_work(long M, long N, long nseg, long seg) {
+GemmWork gemm_bf16_work(long M, long N, long nseg, long seg, bool tn) {
   // sized for 256 compute units; on a device with others the launcher splits
   // within that room
   const GemmPlan pl =
-      plan_bf16(M, N, nseg * ((seg + 63) / 64) * 64, 1, GEMM_SPLIT_MAX_FLOATS, -1, 256);
+      plan_bf16(M, N, nseg * ((seg + 63) / 64) * 64, tn, 1, GEMM_SPLIT_MAX_FLOATS, -1, 256);
   return {pl.split_floats, std::max(pl.colsum_rows(M), (M + 255) / 256) * N};
 }

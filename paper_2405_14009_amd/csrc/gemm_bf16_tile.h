@@ -5,6 +5,7 @@
 
 #include "gemm_bf16_kernel.h"
 #include "gemm_plan.h"
+#include "gemm_small.h"
 
 namespace {
 
@@ -202,8 +203,11 @@ hipError_t launch_tiles(const GemmParams& p, const GemmPlan& pl, hipStream_t s) 
     case TILE_128:
       hipLaunchKernelGGL((gemm_bf16_tile_kernel<128, 128, 2, AK, BKC, EPI>), grid, dim3(256), 0, s, p);
       break;
-    default:
+    case TILE_64:
       hipLaunchKernelGGL((gemm_bf16_tile_kernel<64, 64, 4, AK, BKC, EPI>), grid, dim3(256), 0, s, p);
+      break;
+    default:
+      hipLaunchKernelGGL((gemm_small_kernel<bf16, AK, BKC, EPI>), grid, dim3(256), 0, s, p);
   }
   return hipGetLastError();
 }
@@ -218,7 +222,7 @@ hipError_t launch_bf16(GemmParams p, hipStream_t s) {
   const long z = (long)p.batch * p.heads;
   const bool whole = z == 1 && p.krange == KR_FULL && !p.causal_skip;
   const int cus = device_compute_units();
-  const GemmPlan pl = plan_bf16(p.M, p.N, p.K, z, whole && p.split_work ? p.split_floats : 0,
+  const GemmPlan pl = plan_bf16(p.M, p.N, p.K, !AK && !BKC, z, whole && p.split_work ? p.split_floats : 0,
                                 p.colsum_work != nullptr ? p.colsum_floats : -1, cus);
   if (p.colsum_work != nullptr && pl.colsum_rows(p.M) * p.N > p.colsum_floats) return hipErrorInvalidValue;
   if (p.colsum_work != nullptr) *p.colsum_rows = (int)pl.colsum_rows(p.M);

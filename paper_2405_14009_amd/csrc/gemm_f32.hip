@@ -20,6 +20,7 @@
 // are 4 consecutive k.
 #include "gemm.h"
 #include "gemm_plan.h"
+#include "gemm_small.h"
 #include "mfma_common.h"
 
 namespace {
@@ -284,8 +285,10 @@ hipError_t launch_tiles(const GemmParams& p, const F32Plan& pl, int y, hipStream
   const dim3 grid((unsigned)pl.tiles, (unsigned)y);
   if (pl.bm == 128)
     hipLaunchKernelGGL((gemm_f32_kernel<2, 1, 4, 4, AK, BKC, EPI>), grid, dim3(512), 0, s, p);
-  else
+  else if (pl.bm == 64)
     hipLaunchKernelGGL((gemm_f32_kernel<1, 1, 2, 4, AK, BKC, EPI>), grid, dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((gemm_small_kernel<float, AK, BKC, EPI>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

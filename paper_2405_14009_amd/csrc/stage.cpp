@@ -246,16 +246,16 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
   const long shapes[4][2] = {{h, 3 * h}, {h, h}, {h, f}, {f, h}};  // [in, out] of the linear layers
   for (int i = 0; i < 4; ++i) {
     y.cs_floats[i] = 0;
-    auto product = [&](long M, long N, long nseg, long seg) {
-      const GemmWork g = y.bf ? gemm_bf16_work(M, N, nseg, seg) : gemm_f32_work(M, N, nseg, seg);
+    auto product = [&](long M, long N, long nseg, long seg, bool tn) {
+      const GemmWork g = y.bf ? gemm_bf16_work(M, N, nseg, seg, tn) : gemm_f32_work(M, N, nseg, seg);
       want_split = std::max(want_split, g.split_floats);
       return y.bf ? g.colsum_floats : 0L;
     };
     const long in = shapes[i][0], out = shapes[i][1];
-    product(y.T, out, 1, in);  // Y = X W
-    product(y.T, in, 1, out);  // dX = dY W^T
+    product(y.T, out, 1, in, false);  // Y = X W
+    product(y.T, in, 1, out, false);  // dX = dY W^T
     for (int n = 1; n <= nw; ++n)  // dW = X^T dY of n micro-batches
-      y.cs_floats[i] = std::max(y.cs_floats[i], product(in, out, n, y.T));
+      y.cs_floats[i] = std::max(y.cs_floats[i], product(in, out, n, y.T, true));
   }
   ColJob jobs[COLSUM_MAX_JOBS];
   const int njobs = reductions(y, 0, nullptr, jobs);
