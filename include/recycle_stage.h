@@ -353,13 +353,14 @@ rc_status rc_stage_profile_read(rc_stage* st, rc_kernel_stat* out);
  *                         kernels (fp32 stages, head_dim > 128, and other
  *                         head_dim != 128 at seq_len <= 128);
  *   RC_ATTN_BLOCK         fused online softmax, one workgroup per block of
- *                         128 queries (non-causal, or causal grids that would
- *                         fill the last round of paired workgroups poorly);
+ *                         128 queries (non-causal, or causal unless paired);
  *   RC_ATTN_PAIRED        fused causal, one workgroup per pair of query
- *                         blocks (q, last - q) of equal total length.
+ *                         blocks (q, last - q) of equal total length (grids
+ *                         that fill the compute units once).
  * (Grids of at most one workgroup of 32 queries per compute unit, two for
  * head_dim <= 64, run the fused kernels' form for small grids, whose waves
- * share a block's keys, under either of the two names.)
+ * share a block's keys: reported as RC_ATTN_PAIRED if causal, else
+ * RC_ATTN_BLOCK.)
  * Host only; works on dry-run handles.  Errors: RC_ERR_INVALID_ARG. */
 enum { RC_ATTN_MATERIALISED = 0, RC_ATTN_BLOCK = 1, RC_ATTN_PAIRED = 2 };
 rc_status rc_stage_attention_kernels(rc_stage* st, int32_t* kind);

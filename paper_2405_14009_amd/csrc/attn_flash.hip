@@ -24,16 +24,16 @@ AttnArgs make_args(const void* qkv, int b, int s, int heads, int h) {
   return a;
 }
 
-// The paired kernels run one equal-length workgroup per CU.  They are used
-// when those workgroups fill the CUs of their last round to 90 % or more, or
-// when there are so few that every CU holds at most one anyway (a small
-// problem); otherwise the per-block kernels, whose uneven blocks the
-// hardware packs two to a CU, lose less to the last round.
+// The paired kernels run one workgroup of equal length per CU, the per-block
+// ones two or more of uneven length, longest first.  Pairs win only where they
+// fill the chip once (us, forward + dQ, pairs / blocks: 32 heads of 128,
+// s 2048, 256 pairs, 125 / 134; 16 heads of 64, s 4096, 127 / 159): over
+// several rounds the uneven blocks pack better (96 heads of 128, s 2048, 396 /
+// 320; 128 heads of 64, s 2048, 299 / 227), and on a part of the chip there
+// are more of them (64 heads of 128, s 512, 48 / 38).
 bool pair_grid_fills(long wgs) {
   const long cus = device_compute_units();
-  if (2 * wgs <= cus) return true;
-  const long rounds = (wgs + cus - 1) / cus;
-  return 10 * wgs >= 9 * rounds * cus;
+  return wgs <= cus && 10 * wgs >= 9 * cus;
 }
 
 typedef hipError_t (*Launch)(const AttnArgs&, int, bool, hipStream_t);
@@ -58,9 +58,9 @@ bool attn_flash_supported(int elt, int head_dim, int s) {
   return head_dim == 128 || s > 128;
 }
 
-bool attn_flash_paired(int b, int s, int heads) {
+bool attn_flash_paired(int b, int s, int heads, int head_dim) {
   const int nqb = (s + 127) / 128;
-  return pair_grid_fills((long)((nqb + 1) / 2) * b * heads);
+  return attn_split_grid(s, b * heads, head_dim) || pair_grid_fills((long)((nqb + 1) / 2) * b * heads);
 }
 
 hipError_t attn_flash_forward(const void* qkv, void* o, float* lse, int b, int s, int heads, int h,
@@ -70,7 +70,7 @@ hipError_t attn_flash_forward(const void* qkv, void* o, float* lse, int b, int s
   AttnArgs a = make_args(qkv, b, s, heads, h);
   a.out = (bf16*)o;
   a.lse = lse;
-  return fwd_of(a.d)(a, causal, attn_flash_paired(b, s, heads), st);
+  return fwd_of(a.d)(a, causal, attn_flash_paired(b, s, heads, a.d), st);
 }
 
 hipError_t attn_flash_backward(const void* qkv, const void* o, const void* dout, const float* lse,
@@ -84,5 +84,5 @@ hipError_t attn_flash_backward(const void* qkv, const void* o, const void* dout,
   a.out = (bf16*)dqkv;
   a.lse = (float*)lse;
   a.dv = dv_scratch;
-  return bwd_of(a.d)(a, causal, attn_flash_paired(b, s, heads), st);
+  return bwd_of(a.d)(a, causal, attn_flash_paired(b, s, heads, a.d), st);
 }

@@ -1299,20 +1299,12 @@ __global__ __launch_bounds__(256) void attn_bwd_kv_split_k(AttnArgs p) {
   Attn<HD, FULL>::template attn_bwd_kv_split<CAUSAL>(p);
 }
 
-// Whether the launch takes the kernels of small grids: no more workgroups of
-// 32 rows than compute units hold at once (the tiles of a head of up to 64
-// columns let two share a CU).
-template <int HD>
-bool split_grid(const AttnArgs& a) {
-  return (long)((a.s + 31) / 32) * a.bh <= (HD <= 64 ? 2L : 1L) * device_compute_units();
-}
-
 template <int HD, bool FULL>
 hipError_t attn_fwd_launch(const AttnArgs& a, int causal, bool paired, hipStream_t st) {
   const int nqb = (a.s + 127) / 128;
   const long pairs = (long)((nqb + 1) / 2) * a.bh;
   const dim3 grid((unsigned)(nqb * (long)a.bh));
-  if (split_grid<HD>(a)) {
+  if (attn_split_grid(a.s, a.bh, a.d)) {
     const dim3 g((unsigned)(((a.s + 31) / 32) * (long)a.bh));
     if (causal)
       hipLaunchKernelGGL((attn_fwd_split_k<HD, FULL, true>), g, dim3(256), 0, st, a);
@@ -1335,7 +1327,7 @@ hipError_t attn_bwd_launch(const AttnArgs& a, int causal, bool paired, hipStream
   const int nqb = (a.s + 127) / 128;
   const long pairs = (long)((nqb + 1) / 2) * a.bh;
   const dim3 grid((unsigned)(nqb * (long)a.bh));
-  if (split_grid<HD>(a)) {
+  if (attn_split_grid(a.s, a.bh, a.d)) {
     const dim3 g((unsigned)(((a.s + 31) / 32) * (long)a.bh));
     if (causal) {
       hipLaunchKernelGGL((attn_bwd_q_split_k<HD, FULL, true>), g, dim3(256), 0, st, a);

@@ -70,8 +70,9 @@ hipError_t softmax_backward(int elt, const float* dP, const void* P, void* dS, l
 bool attn_flash_supported(int elt, int head_dim, int s);
 // Whether causal fused attention over b sequences of s tokens and `heads`
 // heads runs the paired kernels (one workgroup per pair of query blocks) on
-// the current device, rather than one workgroup per query block.
-bool attn_flash_paired(int b, int s, int heads);
+// the current device, rather than one workgroup per query block; also true for
+// grids so small that the waves of a workgroup share a block's keys.
+bool attn_flash_paired(int b, int s, int heads, int head_dim);
 hipError_t attn_flash_forward(const void* qkv, void* o, float* lse, int b, int s, int heads, int h,
                               int causal, hipStream_t st);
 hipError_t attn_flash_backward(const void* qkv, const void* o, const void* dout, const float* lse,

@@ -1146,7 +1146,7 @@ rc_status rc_stage_attention_kernels(rc_stage* st, int32_t* kind) {
   if (!st || !kind) return fail(RC_ERR_INVALID_ARG, "null argument");
   const Layout& y = st->lay;
   if (!y.flash) *kind = RC_ATTN_MATERIALISED;
-  else *kind = y.causal && attn_flash_paired(y.b, y.s, y.a) ? RC_ATTN_PAIRED : RC_ATTN_BLOCK;
+  else *kind = y.causal && attn_flash_paired(y.b, y.s, y.a, y.d) ? RC_ATTN_PAIRED : RC_ATTN_BLOCK;
   return RC_OK;
 }
 

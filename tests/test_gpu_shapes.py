@@ -48,8 +48,8 @@ def test_attention_head_widths(d, seq, causal):
 
 @pytest.mark.parametrize("d", [64, 80])
 def test_attention_head_widths_per_block(d):
-    """The per-query-block causal kernels of narrow heads: the grid of pairs
-    would fill the compute units poorly."""
+    """The per-query-block causal kernels of narrow heads (160 pairs of query
+    blocks fill 256 compute units poorly)."""
     from paper_2405_14009_amd import Stage
     cfg = get_config("block_bf16").with_(hidden=10 * d, ffn=20 * d, seq=1000, n_mb=1, rerouted=())
     stage = Stage.from_config(cfg, dry_run=True)
@@ -57,12 +57,23 @@ def test_attention_head_widths_per_block(d):
     check(cfg, 2e-2)
 
 
-@pytest.mark.parametrize("d,causal", [(32, True), (64, True), (64, False), (80, True), (80, False), (120, True)])
-def test_attention_head_widths_paired_and_block(d, causal):
-    """Narrow heads on grids of more 32-row workgroups than compute units hold:
-    the kernels of one workgroup per pair (causal) or block of queries."""
+@pytest.mark.parametrize("d", [32, 64, 80, 120])
+def test_attention_head_widths_paired(d):
+    """Narrow heads on a grid whose pairs of query blocks fill 256 compute units once."""
+    from paper_2405_14009_amd import Stage
+    cfg = get_config("small_bf16").with_(layers=1, hidden=16 * d, heads=16, ffn=8 * d, seq=1000, micro_batch=4, n_mb=1,
+                                         rerouted=())
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert Stage.from_config(cfg, dry_run=True).attention_kernels() == "paired"
+    check(cfg, 2e-2)
+
+
+@pytest.mark.parametrize("d", [32, 64, 80, 120])
+def test_attention_head_widths_blocks_noncausal(d):
+    """Narrow bidirectional heads on a grid of more 32-row workgroups than compute units hold."""
     cfg = get_config("small_bf16").with_(layers=1, hidden=4 * d, heads=4, ffn=8 * d, seq=1128, micro_batch=4, n_mb=1,
-                                         rerouted=(), causal=causal)
+                                         rerouted=(), causal=False)
     check(cfg, 2e-2)
 
 
