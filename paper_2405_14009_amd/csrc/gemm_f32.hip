@@ -187,18 +187,30 @@ __global__ __launch_bounds__(128 * NWN) void gemm_f32_kernel(GemmParams p) {
     __builtin_amdgcn_sched_barrier(0);
     const char* ta = lds + sc * STAGE;
     const char* tb = ta + OpA::BYTES;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
+    const bool refill = i + NST - 1 < nk;
+    // each group of products with the fragment reads of a group of tile i
+    // between them (the last group's go with the one before, so that they are
+    // back at the next barrier), then copies
+    auto reads = [&](int g) {
 #pragma unroll
       for (int q = 0; q < WM; ++q) OpA::frag(ta, 32 * (wm * WM + q) + col, g, hf, fa[set][g][q]);
 #pragma unroll
       for (int q = 0; q < WN; ++q) OpB::frag(tb, 32 * (wn * WN + q) + col, g, hf, fb[set][g][q]);
-    }
-    const bool refill = i + NST - 1 < nk;
+    };
+    constexpr int READS = WM * (AK ? 1 : 4) + WN * (BKC ? 1 : 4);  // read instructions of a group
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       __builtin_amdgcn_sched_barrier(0);
       if (i > 0) products(set ^ 1, g);
+      if (g < NG - 1) reads(g);
+      if (g == NG - 2) reads(NG - 1);
+      if (i > 0) {
+#pragma unroll
+        for (int e = 0; e < 4 * WM * WN; ++e) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, (2 * READS + 4 * WM * WN - 1) / (4 * WM * WN), 0);
+        }
+      }
       __builtin_amdgcn_sched_barrier(0);
       if (refill) {
 #pragma unroll

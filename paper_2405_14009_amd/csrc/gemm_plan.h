@@ -92,15 +92,15 @@ struct F32Plan {
 };
 
 // The same for fp32 products and k-tiles of 32, each segment padded to whole
-// k-tiles.  (A 64x64 k-tile takes 0.70 us alone on its CU, 0.60 beside
-// another, of which the matrix core needs 0.43; a 128x128 one 2.1 of 1.7.)
+// k-tiles.  (A 64x64 k-tile takes 0.66 us alone on its CU, 0.57 beside
+// another, of which the matrix core needs 0.43; a 128x128 one 2.0 of 1.7.)
 inline F32Plan plan_f32(long M, long N, long nseg, long seg, long z, long room_floats, int cus) {
   struct Kind {
     int b;
     GemmCost c;
   };
-  static const Kind kinds[3] = {{128, {7.0, 0.0, 2.1, 2.1, false}},
-                                {64, {4.7, 0.0, 0.70, 0.60, true}},
+  static const Kind kinds[3] = {{128, {7.0, 0.0, 2.0, 2.4, false}},
+                                {64, {4.7, 0.0, 0.66, 0.57, true}},
                                 {32, {3.3, 2.4, 0.19, 0.19, false}}};
   const long nk = std::max(1L, nseg * ((seg + 31) / 32));
   F32Plan best{};
