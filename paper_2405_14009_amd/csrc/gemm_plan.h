@@ -25,7 +25,7 @@ struct GemmCost {
   double us(long wgs, long ktiles, int cus) const {
     auto kt = [&](double load) { return few + (busy - few) * load * load; };
     const double load = (double)wgs / cus;
-    if (two) return fix + ktiles * (load <= 1.0 ? kt(load) : busy * load);
+    if (two) return fix + ktiles * std::max(few, busy * load);
     const long full = wgs / cus;
     const double rest = load - full;
     return fix + again * (full - (rest > 0.0 ? 0 : 1)) + ktiles * (full * busy + (rest > 0.0 ? kt(rest) : 0.0));
@@ -92,7 +92,7 @@ struct F32Plan {
 };
 
 // The same for fp32 products and k-tiles of 32, each segment padded to whole
-// k-tiles.  (A 64x64 k-tile takes 0.66 us alone on its CU, 0.57 beside
+// k-tiles.  (A 64x64 k-tile takes 0.72 us alone on its CU, 0.57 beside
 // another, of which the matrix core needs 0.43; a 128x128 one 2.0 of 1.7.)
 inline F32Plan plan_f32(long M, long N, long nseg, long seg, long z, long room_floats, int cus) {
   struct Kind {
@@ -100,7 +100,7 @@ inline F32Plan plan_f32(long M, long N, long nseg, long seg, long z, long room_f
     GemmCost c;
   };
   static const Kind kinds[3] = {{128, {7.0, 0.0, 2.0, 2.4, false}},
-                                {64, {4.7, 0.0, 0.66, 0.57, true}},
+                                {64, {4.7, 0.0, 0.72, 0.57, true}},
                                 {32, {3.3, 2.4, 0.19, 0.19, false}}};
   const long nk = std::max(1L, nseg * ((seg + 31) / 32));
   F32Plan best{};
