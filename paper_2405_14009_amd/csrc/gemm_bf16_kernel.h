@@ -1,6 +1,7 @@
 // bf16 GEMM kernels on CDNA4 matrix cores: v_mfma_f32_32x32x16_bf16,
 // fp32 accumulate.  Two kernels share the staging and fragment machinery:
-//   gemm_bf16_kernel     256 x 256 workgroup tiles;
+//   gemm_bf16_kernel     256 x 256 workgroup tiles (192 x 256 where the rows of
+//                        A are k-contiguous and that fills the chip better);
 //   gemm_bf16_pp_kernel  256 x 128 tiles with a ping-pong schedule and a
 //                        k-split into two wave groups.
 //
@@ -51,6 +52,14 @@
 #include "mfma_common.h"
 
 namespace {
+
+// Tile of workgroup w of n: workgroups go to the 8 XCDs in turn, each of which
+// takes a consecutive range of the tiles (the first n % 8 one more), so that
+// the tiles an XCD runs at a time share operand panels in its L2.
+__device__ __forceinline__ int xcd_tile(int w, int n) {
+  const int x = w & 7;
+  return x * (n >> 3) + min(x, n & 7) + (w >> 3);
+}
 
 // k-contiguous tiles (64-deep k-tiles, 8 chunks of 16 bytes per row): chunk
 // c (8 elements) of row r lives at chunk c ^ swz_k<BK>(r).  Depends on r mod
@@ -428,10 +437,10 @@ template <int BM, int BN, int NW, int KS, int BK, int NST, bool AK, bool BKC, in
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   // the configuration the launcher uses (256 x 128 tiles run the ping-pong
   // kernel, which owns the k-split)
-  static_assert(BM == 256 && BN == 256 && NW == 8 && KS == 1 && BK == 64 && NST >= 2, "tile shapes");
+  static_assert((BM == 256 || (BM == 192 && AK)) && BN == 256 && NW == 8 && KS == 1 && BK == 64 && NST >= 2, "tile shapes");
   constexpr int NWS = NW / KS;           // waves per k-group
   constexpr int WN_ = NWS / 2;           // waves along n (2 along m)
-  constexpr int TN = BN / (32 * WN_);    // 32-wide blocks per wave along n
+  constexpr int TM = BM / 64, TN = BN / (32 * WN_);  // 32-wide blocks per wave
   constexpr int NKS = (BK / 16) / KS;    // k-steps per wave per k-tile
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
   constexpr int STAGE = A_BYTES + B_BYTES;
@@ -452,9 +461,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   // Tile order: spread consecutive tiles over the 8 XCDs' own ranges, then
   // group tile-rows so concurrently running tiles share operand panels in L2.
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  int pid = blockIdx.x;
-  const int ntiles = gridDim.x;
-  if ((ntiles & 7) == 0) pid = (pid & 7) * (ntiles >> 3) + (pid >> 3);
+  const int pid = xcd_tile(blockIdx.x, gridDim.x);
   constexpr int GM = 8;
   const int width = GM * tiles_n;
   const int first_m = (pid / width) * GM;
@@ -484,14 +491,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   Copier<BN, BKC, NIB, NW, BK> cb;
   ca.init(wave, p.lda, m0, lane);
   cb.init(wave, p.ldb, n0, lane);
-  FragOffsets<BM, AK, 4, NKS, BK> fa;
+  FragOffsets<BM, AK, TM, NKS, BK> fa;
   FragOffsets<BN, BKC, TN, NKS, BK> fb;
-  fa.init(wm * 128, lane, kg * NKS);
+  fa.init(wm * (BM / 2), lane, kg * NKS);
   fb.init(wn * (BN / WN_), lane, kg * NKS);
 
-  f32x16 acc[4][TN];
+  f32x16 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -523,8 +530,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
   // 1-4 % shorter products there; the other layouts measured slower with it.
   static_assert(NKS >= 2, "the refill spans two k-steps");
   constexpr bool DEFER = !AK && !BKC;
-  bf16x8 pa[4], pb[TN];
-  mma_pending_clear<4, TN>(pa, pb);
+  bf16x8 pa[TM], pb[TN];
+  mma_pending_clear<TM, TN>(pa, pb);
 #pragma unroll
   for (int i = 0; i < NST - 1; ++i)
     if (i < nk) issue(lds + i * STAGE);
@@ -538,7 +545,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
     const bool refill = t + NST - 1 < nk;
     char* dst = lds + si * STAGE;
     const char* st = lds + sc * STAGE;
-    mma_tile<BM, BN, AK, BKC, 4, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
+    mma_tile<BM, BN, AK, BKC, TM, TN, NKS, BK, DEFER>(acc, st, st + A_BYTES, fa, fb, [&](int ks) {
       if (refill && ks == 0) ca.issue(wk.a, dst, wave, p.lda, p.M, wk.k, wk.kend);
       if (refill && ks == 1) cb.issue(wk.b, dst + A_BYTES, wave, p.ldb, p.N, wk.k, wk.kend);
     }, pa, pb);
@@ -555,7 +562,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
     si = si + 1 == NST ? 0 : si + 1;
   }
 
-  if constexpr (DEFER) mma_flush<4, TN>(acc, pa, pb);
+  if constexpr (DEFER) mma_flush<TM, TN>(acc, pa, pb);
   // LDS is free once every wave is past its last k-tile.
   __builtin_amdgcn_sched_barrier(0);
   __syncthreads();
@@ -564,7 +571,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_kernel(GemmParams p) {
     if (cs_on) cs.finish((float*)lds, p, split * tiles_m + tm, n0, threadIdx.x);
   }
   float* sm = (float*)(lds + wave * EPI_BYTES);
-  epilogue<EPI, TN, 0, 4>(p, acc, sm, m0 + wm * 128, n0 + wn * (BN / WN_), lane, c_off);
+  epilogue<EPI, TN, 0, TM, true, TM>(p, acc, sm, m0 + wm * (BM / 2), n0 + wn * (BN / WN_), lane, c_off);
 }
 
 // Persistent form of gemm_bf16_kernel (256 x 256 tiles, 8 waves, two-stage
@@ -803,9 +810,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmParams p) {
   const int wm = ws / WN_, wn = ws % WN_;
 
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  int pid = blockIdx.x;
-  const int ntiles = gridDim.x;
-  if ((ntiles & 7) == 0) pid = (pid & 7) * (ntiles >> 3) + (pid >> 3);
+  const int pid = xcd_tile(blockIdx.x, gridDim.x);
   const int width = GM * tiles_n;
   const int first_m = (pid / width) * GM;
   const int gsz = min(tiles_m - first_m, GM);

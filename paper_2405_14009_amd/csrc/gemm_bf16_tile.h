@@ -31,11 +31,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(GemmParams p) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  const int ntiles = tiles_m * tiles_n;
+  const int tiles_m = (p.M + BM - 1) / BM;
   // consecutive tiles (down a column of tiles, which share a B panel) on one XCD
-  int tile = blockIdx.x;
-  if ((ntiles & 7) == 0) tile = (tile & 7) * (ntiles >> 3) + (tile >> 3);
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int tm = tile % tiles_m, tn = tile / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
   if (p.causal_skip && n0 > m0 + BM - 1) return;
@@ -197,6 +195,12 @@ hipError_t launch_tiles(const GemmParams& p, const GemmPlan& pl, hipStream_t s) 
       }
       hipLaunchKernelGGL((gemm_bf16_kernel<256, 256, 8, 1, 64, 2, AK, BKC, EPI>), grid, dim3(512), 0, s, p);
       break;
+    case TILE_192x256:
+      if constexpr (AK) {
+        hipLaunchKernelGGL((gemm_bf16_kernel<192, 256, 8, 1, 64, 2, AK, BKC, EPI>), grid, dim3(512), 0, s, p);
+        break;
+      }
+      return hipErrorInvalidValue;
     case TILE_256x128:
       hipLaunchKernelGGL((gemm_bf16_pp_kernel<128, 2, 3, 4, AK, BKC, EPI>), grid, dim3(512), 0, s, p);
       break;

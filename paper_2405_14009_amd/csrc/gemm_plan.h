@@ -4,7 +4,7 @@
 
 #include <algorithm>
 
-enum GemmTile { TILE_256 = 0, TILE_256x128 = 1, TILE_128 = 2, TILE_64 = 3, TILE_32 = 4 };
+enum GemmTile { TILE_256 = 0, TILE_256x128 = 1, TILE_128 = 2, TILE_64 = 3, TILE_32 = 4, TILE_192x256 = 5 };
 
 struct GemmPlan {
   GemmTile tile;
@@ -55,17 +55,19 @@ inline GemmPlan plan_bf16(long M, long N, long K, bool tn, long z, long room_flo
     int bm, bn;
     GemmCost c;
   };
-  const Kind kinds[5] = {
-      {TILE_256, 256, 256, {12.7, 3.2, 1.09, 1.50, false}},
-      {TILE_256x128, 256, 128, {9.8, 2.5, tn ? 0.76 : 0.61, tn ? 1.00 : 0.95, false}},
+  const Kind kinds[6] = {
+      {TILE_256, 256, 256, {14.0, 10.0, 1.09, 1.50, false}},
+      {TILE_256x128, 256, 128, {9.8, 2.5, tn ? 0.76 : 0.61, tn ? 1.00 : 0.97, false}},
       {TILE_128, 128, 128, {7.5, 0.0, 0.62, 0.68, true}},
       {TILE_64, 64, 64, {4.0, 0.0, 0.25, 0.28, true}},
       {TILE_32, 32, 32, {3.6, 2.4, 0.07, 0.10, false}},
+      {TILE_192x256, 192, 256, {12.0, 3.2, 0.96, 1.31, false}},
   };
   const long nk = std::max(1L, (K + 63) / 64);
   GemmPlan best{};
   double best_us = 1e30;
   for (const Kind& q : kinds) {
+    if (tn && q.t == TILE_192x256) continue;  // whole 64-row blocks of a k-contiguous A only
     const long rows = (M + q.bm - 1) / q.bm, tiles = rows * ((N + q.bn - 1) / q.bn);
     for (int want = 1; want <= (q.t == TILE_32 ? 1 : 32); ++want) {
       const long per = (nk + want - 1) / want;

@@ -95,6 +95,14 @@ def test_product_shapes(dtype, shape):
     check(cfg, 1e-5 if dtype == "f32" else 2e-2)
 
 
+def test_192_row_tiles():
+    """FC1 forward and FC2 input gradient of [1800, 5032] over 768 fill 256
+    compute units best in 192x256 tiles, ragged in both directions and in a
+    tile count that is no multiple of the XCDs."""
+    check(get_config("small_bf16").with_(layers=1, hidden=768, heads=6, ffn=5032, seq=600, micro_batch=3, n_mb=1,
+                                         rerouted=()), 2e-2)
+
+
 def test_split_products_are_reproducible():
     """Partials of split reductions are added in a fixed order: the same
     iteration twice gives the same bits."""
