@@ -71,19 +71,27 @@ def sources_digest(d: str = None) -> str:
 
 
 def kernel_class(name: str) -> str:
-    # the one-tile and ping-pong bf16 GEMM kernels end their template arguments
-    # with (A k-contiguous, B k-contiguous, epilogue); the persistent kernel
-    # begins with (epilogue, A k-contiguous, B k-contiguous)
+    # the one-tile, ping-pong and small-tile bf16 GEMM kernels end their template
+    # arguments with (A k-contiguous, B k-contiguous, epilogue); the persistent
+    # kernel begins with (epilogue, A k-contiguous, B k-contiguous); the sum of a
+    # split product's partials begins with the epilogue
+    m = re.search(r"splitk_finish_k(?:<|ILi)(\d+)", name)
+    if m:
+        return {1: "gemm_fwd", 2: "gemm_fwd", 3: "gemm_fwd", 5: "gemm_wgrad"}.get(int(m.group(1)), "gemm_dgrad")
+    if re.search(r"gemm_small_kernel<float", name):
+        return "gemm_f32"
     m = re.search(r"gemm_bf16_persist_kernel<(\d+),\s*(true|false),\s*(true|false)(?:,\s*(?:true|false))?>", name)
     if m:
         epi, ak, bk = int(m.group(1)), m.group(2), m.group(3)
     else:
-        m = re.search(r"gemm_bf16(?:_pp)?_kernel<[^>]*?(true|false),\s*(true|false),\s*(\d+)>", name)
+        m = re.search(r"gemm_(?:bf16(?:_pp|_tile)?|small)_kernel<[^>]*?(true|false),\s*(true|false),\s*(\d+)>", name)
         if m:
             ak, bk, epi = m.group(1), m.group(2), int(m.group(3))
     if m:
         if (ak, bk) == ("false", "false"):
             return "gemm_wgrad"
+        if (ak, bk, epi) == ("true", "false", 6):  # partials of a split forward product
+            return "gemm_fwd"
         if epi in (1, 2, 3):          # bias / bias + residual / bias + GeLU: the forward products
             return "gemm_fwd"
         if (ak, bk) == ("true", "true") and epi in (0, 4):
@@ -91,7 +99,7 @@ def kernel_class(name: str) -> str:
         return "gemm_other"
     if "gemm_f32" in name:
         return "gemm_f32"
-    if re.search(r"attn_fwd(_pair)?_k", name):
+    if re.search(r"attn_fwd(_pair|_split)?_k", name):
         return "attn_fwd"
     if "attn_bwd" in name:
         return "attn_bwd"
