@@ -90,8 +90,6 @@ def kernel_class(name: str) -> str:
     if m:
         if (ak, bk) == ("false", "false"):
             return "gemm_wgrad"
-        if (ak, bk, epi) == ("true", "false", 6):  # partials of a split forward product
-            return "gemm_fwd"
         if epi in (1, 2, 3):          # bias / bias + residual / bias + GeLU: the forward products
             return "gemm_fwd"
         if (ak, bk) == ("true", "true") and epi in (0, 4):
