@@ -12,7 +12,8 @@ namespace {
 // One tile (and split) per workgroup of four waves.  The ring of NST stages
 // works as in gemm_bf16_kernel: one barrier per k-tile, NST - 1 k-tiles in
 // flight.  At these sizes the kernel is bound by the latency of that chain
-// (about 0.35 us per k-tile with one workgroup per CU), so the ring is as deep
+// (0.25 us per k-tile of 64 for 64x64 tiles with one workgroup per CU, 0.35
+// before the multiply ran one k-tile behind the reads), so the ring is as deep
 // as two workgroups per CU allow and the launcher splits the reduction until
 // the CUs are filled.
 template <int BM, int BN, int NST, bool AK, bool BKC, int EPI>
