@@ -12,6 +12,7 @@ AttnArgs make_args(const void* qkv, int b, int s, int heads, int h) {
   a.o = nullptr;
   a.dout = nullptr;
   a.out = nullptr;
+  a.orest = nullptr;
   a.lse = nullptr;
   a.dv = nullptr;
   a.s = s;
@@ -63,23 +64,27 @@ bool attn_flash_paired(int b, int s, int heads, int head_dim) {
   return attn_split_grid(s, b * heads, head_dim) || pair_grid_fills((long)((nqb + 1) / 2) * b * heads);
 }
 
-hipError_t attn_flash_forward(const void* qkv, void* o, float* lse, int b, int s, int heads, int h,
+bool attn_flash_keeps_rest(int head_dim) { return head_dim != 128; }
+
+hipError_t attn_flash_forward(const void* qkv, void* o, void* orest, float* lse, int b, int s, int heads, int h,
                               int causal, hipStream_t st) {
-  if (!args_ok(heads, h)) return hipErrorInvalidValue;
+  if (!args_ok(heads, h) || (attn_flash_keeps_rest(h / heads) && !orest)) return hipErrorInvalidValue;
   if (b <= 0 || s <= 0) return hipSuccess;
   AttnArgs a = make_args(qkv, b, s, heads, h);
   a.out = (bf16*)o;
+  a.orest = (bf16*)orest;
   a.lse = lse;
   return fwd_of(a.d)(a, causal, attn_flash_paired(b, s, heads, a.d), st);
 }
 
-hipError_t attn_flash_backward(const void* qkv, const void* o, const void* dout, const float* lse,
-                               float* dv_scratch, void* dqkv, int b, int s, int heads, int h, int causal,
-                               hipStream_t st) {
-  if (!args_ok(heads, h)) return hipErrorInvalidValue;
+hipError_t attn_flash_backward(const void* qkv, const void* o, const void* orest, const void* dout,
+                               const float* lse, float* dv_scratch, void* dqkv, int b, int s, int heads, int h,
+                               int causal, hipStream_t st) {
+  if (!args_ok(heads, h) || (attn_flash_keeps_rest(h / heads) && !orest)) return hipErrorInvalidValue;
   if (b <= 0 || s <= 0) return hipSuccess;
   AttnArgs a = make_args(qkv, b, s, heads, h);
   a.o = (const bf16*)o;
+  a.orest = (bf16*)orest;
   a.dout = (const bf16*)dout;
   a.out = (bf16*)dqkv;
   a.lse = (float*)lse;

@@ -63,7 +63,9 @@ hipError_t softmax_backward(int elt, const float* dP, const void* P, void* dS, l
 // o: [b*s, h]; lse: [b, heads, s] fp32 base-2 log-sum-exp of the scaled scores
 // (written by the forward, read by the backward).  The backward writes dQ, dK,
 // dV into the three column blocks of dqkv [b*s, 3h]; dv_scratch holds b*heads*s
-// floats.  h == heads * d.  Head dimensions other than 128 take it for
+// floats.  h == heads * d.  orest [b*s, h] (written by the forward, read by the
+// backward; unused where attn_flash_keeps_rest says no): what the bf16 rounding
+// of o drops.  Head dimensions other than 128 take it for
 // sequences of more than one query block (128); up to that the materialised
 // kernels stay, whose probabilities are small there, as stages of short
 // sequences and narrow heads report through rc_stage_attention_kernels.
@@ -73,11 +75,12 @@ bool attn_flash_supported(int elt, int head_dim, int s);
 // the current device, rather than one workgroup per query block; also true for
 // grids so small that the waves of a workgroup share a block's keys.
 bool attn_flash_paired(int b, int s, int heads, int head_dim);
-hipError_t attn_flash_forward(const void* qkv, void* o, float* lse, int b, int s, int heads, int h,
+bool attn_flash_keeps_rest(int head_dim);
+hipError_t attn_flash_forward(const void* qkv, void* o, void* orest, float* lse, int b, int s, int heads, int h,
                               int causal, hipStream_t st);
-hipError_t attn_flash_backward(const void* qkv, const void* o, const void* dout, const float* lse,
-                               float* dv_scratch, void* dqkv, int b, int s, int heads, int h, int causal,
-                               hipStream_t st);
+hipError_t attn_flash_backward(const void* qkv, const void* o, const void* orest, const void* dout,
+                               const float* lse, float* dv_scratch, void* dqkv, int b, int s, int heads, int h,
+                               int causal, hipStream_t st);
 
 // AdamW over n fp32 parameters; weight decay on indices < n_decay; when wb is
 // non-null the first n_decay updated values are also written to it in bf16.

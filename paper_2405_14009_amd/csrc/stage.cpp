@@ -64,8 +64,9 @@ struct FLayer {
   // Dg: gelu'(U) of the FFN, which the FC2 input gradient multiplies by (the
   // forward stores it instead of U: the same information for B_input, and the
   // derivative is formed where the fp32 U is at hand).  P: attention
-  // probabilities, or the row log-sum-exp (fused attention).
-  size_t QKV, Dg, P, bytes;
+  // probabilities, or the row log-sum-exp (fused attention).  Or: what the
+  // bf16 rounding of O drops (fused attention below head dimension 128).
+  size_t QKV, Dg, P, Or, bytes;
 };
 
 struct Layout {
@@ -213,6 +214,7 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
   y.fl.QKV = take(T * 3 * h * E);
   y.fl.Dg = take(T * f * E);
   y.fl.P = take(y.flash ? rows * 4 : ss * E);
+  y.fl.Or = take(y.flash && attn_flash_keeps_rest(d) ? T * h * E : 0);
   y.fl.bytes = o;
   y.wslot_bytes = (size_t)y.L * w.bytes;
   y.fslot_bytes = (size_t)y.L * y.fl.bytes;
@@ -232,7 +234,7 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
   {
     const uint64_t Th = (uint64_t)T * h, Tf = (uint64_t)T * f, st = 16ull * T;
     // Head dimensions other than 128 count the probabilities also where the
-    // fused kernels keep only the row statistics, so that limits and op lists
+    // fused kernels keep less (row statistics and O's rest), so that limits and op lists
     // planned with these figures stay valid whichever kernels run.
     const uint64_t attn = y.bf && d == 128 ? 4ull * rows : (uint64_t)E * ss;
     y.acct_af = (uint64_t)y.L * (E * (8 * Th + 2 * Tf) + st + attn);
@@ -336,7 +338,7 @@ struct WPtr {
   float *mu1, *r1, *mu2, *r2;
 };
 struct FPtr {
-  char *QKV, *Dg, *P;
+  char *QKV, *Dg, *P, *Or;
 };
 
 WPtr wptr(rc_stage* st, int slot, int l) {
@@ -351,7 +353,7 @@ WPtr wptr(rc_stage* st, int slot, int l) {
 FPtr fptr(rc_stage* st, int slot, int l) {
   const Layout& y = st->lay;
   char* b = st->stash + y.off_fslots + (size_t)slot * y.fslot_bytes + (size_t)l * y.fl.bytes;
-  return {b + y.fl.QKV, b + y.fl.Dg, b + y.fl.P};
+  return {b + y.fl.QKV, b + y.fl.Dg, b + y.fl.P, b + y.fl.Or};
 }
 
 float* master(rc_stage* st, int l, int pid) {
@@ -453,11 +455,11 @@ void batch_heads(GemmParams& g, const Layout& y, long a_bs, long a_hs, long b_bs
   g.c_hs = c_hs;
 }
 
-rc_status attn_forward(rc_stage* st, char* QKV, char* P, char* O) {
+rc_status attn_forward(rc_stage* st, char* QKV, char* P, char* O, char* Or) {
   const Layout& y = st->lay;
   const int E = y.elt;
   if (y.flash) {
-    HIPCHK(attn_flash_forward(QKV, O, (float*)P, y.b, y.s, y.a, y.h, y.causal, st->stream));
+    HIPCHK(attn_flash_forward(QKV, O, Or, (float*)P, y.b, y.s, y.a, y.h, y.causal, st->stream));
     return RC_OK;
   }
   const long s = y.s, h = y.h, d = y.d, ss = s * s;
@@ -475,11 +477,11 @@ rc_status attn_forward(rc_stage* st, char* QKV, char* P, char* O) {
   return RC_OK;
 }
 
-rc_status attn_backward(rc_stage* st, char* QKV, char* P, char* O, char* dO, char* dQKV) {
+rc_status attn_backward(rc_stage* st, char* QKV, char* P, char* O, char* Or, char* dO, char* dQKV) {
   const Layout& y = st->lay;
   const int E = y.elt;
   if (y.flash) {
-    HIPCHK(attn_flash_backward(QKV, O, dO, (const float*)P, (float*)(st->work + y.off_dv), dQKV, y.b,
+    HIPCHK(attn_flash_backward(QKV, O, Or, dO, (const float*)P, (float*)(st->work + y.off_dv), dQKV, y.b,
                                y.s, y.a, y.h, y.causal, st->stream));
     return RC_OK;
   }
@@ -531,7 +533,7 @@ rc_status run_forward(rc_stage* st, int ws, int fs, const void* x, void* yout) {
     HIPCHK(gemm_lin(st, g, RC_K_GEMM_FWD));
     {
       Prof pa(st, RC_K_ATTN_FWD, 2.0 * att, 4.0 * T * h * E);
-      rc_status r = attn_forward(st, fl.QKV, fl.P, w.O);
+      rc_status r = attn_forward(st, fl.QKV, fl.P, w.O, fl.Or);
       if (r != RC_OK) return r;
     }
     g = gp(T, h, h, w.O, h, 1, weight(st, l, RC_P_W_O), h, 0, EPI_BIAS_RESID, w.H, h);
@@ -597,7 +599,7 @@ rc_status run_backward_input(rc_stage* st, int ws, int fs, const void* dy, void*
     HIPCHK(gemm_lin(st, g, RC_K_GEMM_DGRAD));
     {
       Prof pa(st, RC_K_ATTN_BWD, 4.0 * att, 8.0 * T * h * E);
-      rc_status r = attn_backward(st, fl.QKV, fl.P, w.O, dO, w.dQKV);
+      rc_status r = attn_backward(st, fl.QKV, fl.P, w.O, fl.Or, dO, w.dQKV);
       if (r != RC_OK) return r;
     }
     // dA = dQKV W_qkv^T
