@@ -18,6 +18,7 @@ AttnArgs make_args(const void* qkv, int b, int s, int heads, int h) {
   a.s = s;
   a.heads = heads;
   a.bh = b * heads;
+  a.rows = (long)b * heads * s;
   a.h = h;
   a.d = h / heads;
   a.scale = 1.0f / std::sqrt((float)(h / heads));
@@ -64,11 +65,11 @@ bool attn_flash_paired(int b, int s, int heads, int head_dim) {
   return attn_split_grid(s, b * heads, head_dim) || pair_grid_fills((long)((nqb + 1) / 2) * b * heads);
 }
 
-bool attn_flash_keeps_rest(int head_dim) { return head_dim != 128; }
+bool attn_flash_narrow(int head_dim) { return head_dim != 128; }
 
 hipError_t attn_flash_forward(const void* qkv, void* o, void* orest, float* lse, int b, int s, int heads, int h,
                               int causal, hipStream_t st) {
-  if (!args_ok(heads, h) || (attn_flash_keeps_rest(h / heads) && !orest)) return hipErrorInvalidValue;
+  if (!args_ok(heads, h) || (attn_flash_narrow(h / heads) && !orest)) return hipErrorInvalidValue;
   if (b <= 0 || s <= 0) return hipSuccess;
   AttnArgs a = make_args(qkv, b, s, heads, h);
   a.out = (bf16*)o;
@@ -80,7 +81,7 @@ hipError_t attn_flash_forward(const void* qkv, void* o, void* orest, float* lse,
 hipError_t attn_flash_backward(const void* qkv, const void* o, const void* orest, const void* dout,
                                const float* lse, float* dv_scratch, void* dqkv, int b, int s, int heads, int h,
                                int causal, hipStream_t st) {
-  if (!args_ok(heads, h) || (attn_flash_keeps_rest(h / heads) && !orest)) return hipErrorInvalidValue;
+  if (!args_ok(heads, h) || (attn_flash_narrow(h / heads) && !orest)) return hipErrorInvalidValue;
   if (b <= 0 || s <= 0) return hipSuccess;
   AttnArgs a = make_args(qkv, b, s, heads, h);
   a.o = (const bf16*)o;

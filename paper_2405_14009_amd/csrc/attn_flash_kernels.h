@@ -7,6 +7,13 @@
 //   forward   one pass over key blocks with a running row maximum and row sum
 //             (the softmax is rescaled as the maximum grows); O and the row
 //             log-sum-exp (base 2, of the scaled scores) are written.
+//             (Head dimensions below 128 keep the row's reference maximum, of
+//             the scores as they are, apart from the logarithm of its sum: the
+//             exponents are then differences of scores, and P is as exact for
+//             scores of any size as stored probabilities were.  Scaled scores
+//             rounded into one log-sum-exp lose 2^-24 of themselves: q and k of
+//             100 times unit variance, d 64, rel-L2 of dQ 8e-2 against 1.2e-3,
+//             and beyond 2^31 the exponentials overflow.)
 //   backward  P is recomputed from Q, K and the stored log-sum-exp;
 //             Dv = rowsum(dO o O) (= rowsum(dP o P));  dS = P o (dP - Dv);
 //             (head dimensions below 128 take O unrounded there: the forward also
@@ -57,9 +64,12 @@ struct AttnArgs {
   const bf16* dout; // [b*s, h]
   bf16* out;        // forward: O [b*s, h];  backward: dQKV [b*s, 3h]
   bf16* orest;      // [b*s, h]  O before its rounding minus o (head dimensions below 128)
-  float* lse;       // [b, heads, s]  base-2 log-sum-exp of the scaled scores
+  float* lse;       // [b, heads, s]  base-2 log-sum-exp of the scaled scores; below head
+                    // dimension 128 the reference score, then as many floats with
+                    // log2 of the sum relative to it
   float* dv;        // [b, heads, s]  rowsum(dO o O)
   int s, heads, bh, h, d;
+  long rows;          // b * heads * s
   float scale, sl2;  // 1/sqrt(d), 1/sqrt(d) * log2(e)
 };
 
@@ -97,6 +107,9 @@ static __device__ __forceinline__ void load_tile(const i32x4& rs, char* tile, in
     dma16(rs, __builtin_amdgcn_readfirstlane(lds_addr(tile) + (wave + 4 * j) * 1024), off);
   }
 }
+
+// Row vectors of a block of queries in LDS, 1 KB each: statistics and Dv.
+static constexpr int VECS = FULL ? 2048 : 3072;
 
 // 64 floats (one per row of a 64-row block, rows >= nrows as zeros) into a
 // 1 KB LDS area; issued by one wave.
@@ -314,8 +327,27 @@ static __device__ __forceinline__ void block_of(const AttnArgs& p, int nblk, boo
 // O^T += V^T P^T (16 MFMAs).
 
 // Online-softmax state of a wave's 32 queries: unnormalised O^T, the
-// reference maximum (base-2 scaled score units) and this lane's share of the
-// row sum (lanes l and l + 32 hold the two halves of each key block's rows).
+// reference maximum (base-2 scaled score units for head dimension 128, scores
+// otherwise) and this lane's share of the row sum (lanes l and l + 32 hold the
+// two halves of each key block's rows).
+static __device__ __forceinline__ constexpr float m_none() { return FULL ? -1e30f : -3.402823466e38f; }
+// 2^(a - b) of two reference maxima.
+static __device__ __forceinline__ float exp_diff(float a, float b, const AttnArgs& p) {
+  return __builtin_amdgcn_exp2f(FULL ? a - b : (a - b) * p.sl2);
+}
+// P of score sc in a row of statistics (ref, ls): see AttnArgs::lse.
+static __device__ __forceinline__ float prob(float sc, float ref, float ls, const AttnArgs& p) {
+  return __builtin_amdgcn_exp2f(FULL ? sc * p.sl2 - ref : fmaf(sc - ref, p.sl2, -ls));
+}
+// Statistics of row i from its reference maximum and sum.
+static __device__ __forceinline__ void store_stats(const AttnArgs& p, long i, float m, float l) {
+  if constexpr (FULL) {
+    p.lse[i] = m + __builtin_amdgcn_logf(l);
+  } else {
+    p.lse[i] = m;
+    p.lse[p.rows + i] = __builtin_amdgcn_logf(l);
+  }
+}
 struct FwdState {
   f32x16 o[HD / 32];
   float m_run, l_run;
@@ -324,7 +356,7 @@ struct FwdState {
   __device__ __forceinline__ void reset() {
 #pragma unroll
     for (int b = 0; b < HD / 32; ++b) zero(o[b]);
-    m_run = -1e30f;
+    m_run = m_none();
     l_run = 0.f;
   }
 };
@@ -370,22 +402,23 @@ static __device__ __forceinline__ void fwd_block(FwdState& st, const bf16x8 (&qf
   // Masked keys (past the sequence end or, causal, after the query) at -inf.
   if (uniform((CAUSAL && k0 + 63 > q0) || k0 + 64 > p.s))
     mask_scores<2>(sc, key_room<CAUSAL>(k0, qq, lane, p), -INFINITY);
-  // Row maximum over the raw scores (the scale is positive); the scale is
-  // folded into the exponent's FMA below.
+  // Row maximum over the raw scores (the scale is positive); for head dimension
+  // 128 the scale is folded into the exponent's FMA below.
   float mx = -INFINITY;
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[j][r]);
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * p.sl2;
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  if constexpr (FULL) mx *= p.sl2;
   // Lazy rescaling: the reference maximum moves only when a row's maximum
   // exceeds it by more than 8 (base 2), so most key blocks skip rescaling O
   // and the row sum.  Exponentials are then at most 2^8, and O / l and the
   // log-sum-exp are unchanged in exact arithmetic.
-  const bool grow = mx > st.m_run + 8.f;
+  const bool grow = FULL ? mx > st.m_run + 8.f : (mx - st.m_run) * p.sl2 > 8.f;
   if (__any(grow)) {
     const float m_new = grow ? mx : st.m_run;
-    const float alpha = __builtin_amdgcn_exp2f(st.m_run - m_new);
+    const float alpha = exp_diff(st.m_run, m_new, p);
     st.m_run = m_new;
     st.l_run *= alpha;
 #pragma unroll
@@ -398,7 +431,7 @@ static __device__ __forceinline__ void fwd_block(FwdState& st, const bf16x8 (&qf
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float e = __builtin_amdgcn_exp2f(fmaf(sc[j][r], p.sl2, -st.m_run));
+      const float e = __builtin_amdgcn_exp2f(FULL ? fmaf(sc[j][r], p.sl2, -st.m_run) : (sc[j][r] - st.m_run) * p.sl2);
       sc[j][r] = e;
       ls += e;
     }
@@ -433,7 +466,7 @@ static __device__ __forceinline__ void fwd_store(FwdState& st, const AttnArgs& p
     else
       store_dT(st.o, rest, p.h, qq, p.s, lane, 1.0f, dim(p));
   }
-  if (lane < 32 && qq < p.s) p.lse[(long)z * p.s + qq] = st.m_run + __builtin_amdgcn_logf(l_tot);
+  if (lane < 32 && qq < p.s) store_stats(p, (long)z * p.s + qq, st.m_run, l_tot);
 }
 
 // One query block of 128 per workgroup (4 waves), two stages of K and V.
@@ -612,7 +645,7 @@ static __device__ __forceinline__ void attn_fwd_pair(const AttnArgs& p) {
   if (grp == 1) {
     const float2 ml = mstat[wg * 64 + lane];
     const float m = fmaxf(ml.x, st.m_run);
-    const float a0 = __builtin_amdgcn_exp2f(ml.x - m), a1 = __builtin_amdgcn_exp2f(st.m_run - m);
+    const float a0 = exp_diff(ml.x, m, p), a1 = exp_diff(st.m_run, m, p);
     const float4* src = (const float4*)lds + wg * (HD / 8) * 64 + lane;
 #pragma unroll
     for (int b = 0; b < HD / 32; ++b)
@@ -642,6 +675,7 @@ static __device__ __forceinline__ void bwdkv_block(f32x16 (&dk)[HD / 32], f32x16
   const char* ot = st + TILE64;
   const float* lse = (const float*)(st + 2 * TILE64);
   const float* dvv = (const float*)(st + 2 * TILE64 + 1024);
+  const float* lsum = (const float*)(st + 2 * TILE64 + 2048);
   const bool need_mask = uniform(CAUSAL && qs < k0w + 31);
   // the two 32-query halves of the block in turn (one half's scores live)
 #pragma unroll 1
@@ -657,12 +691,15 @@ static __device__ __forceinline__ void bwdkv_block(f32x16 (&dk)[HD / 32], f32x16
       const float4 L4 = *(const float4*)(lse + ql);
       const float4 D4 = *(const float4*)(dvv + ql);
       const float Lv[4] = {L4.x, L4.y, L4.z, L4.w};
+      float4 S4 = make_float4(0.f, 0.f, 0.f, 0.f);
+      if constexpr (!FULL) S4 = *(const float4*)(lsum + ql);
+      const float Sv[4] = {S4.x, S4.y, S4.z, S4.w};
       Dv[4 * rg] = D4.x;
       Dv[4 * rg + 1] = D4.y;
       Dv[4 * rg + 2] = D4.z;
       Dv[4 * rg + 3] = D4.w;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sc[4 * rg + e] = __builtin_amdgcn_exp2f(sc[4 * rg + e] * p.sl2 - Lv[e]);
+      for (int e = 0; e < 4; ++e) sc[4 * rg + e] = prob(sc[4 * rg + e], Lv[e], Sv[e], p);
     }
     // element r holds query qs + 32 j + 4 (l / 32) + kofs(r): masked when
     // that query precedes this lane's key
@@ -693,10 +730,10 @@ static __device__ __forceinline__ void bwdkv_block(f32x16 (&dk)[HD / 32], f32x16
 // head), 4 waves x 32 keys (K and V rows stationary in registers); query
 // blocks of 64 staged in LDS (Q, dO, log-sum-exp and Dv; two stages).  Per
 // wave and query block: S = Q K^T and dP = dO V^T (lane column = key),
-// P = exp2(S sl2 - lse), dS = P (dP - Dv); dV^T += dO^T P, dK^T += Q^T dS.
+// P from the row statistics, dS = P (dP - Dv); dV^T += dO^T P, dK^T += Q^T dS.
 template <bool CAUSAL>
 static __device__ __forceinline__ void attn_bwd_kv(const AttnArgs& p) {
-  constexpr int STAGE = 2 * TILE64 + 2048;
+  constexpr int STAGE = 2 * TILE64 + VECS;
   __shared__ __attribute__((aligned(1024))) char lds0[STAGE];
   __shared__ __attribute__((aligned(1024))) char lds1[STAGE];
   const int lane = threadIdx.x & 63;
@@ -713,6 +750,7 @@ static __device__ __forceinline__ void attn_bwd_kv(const AttnArgs& p) {
   const i32x4 rq = make_rsrc(Q, 2L * p.s * ld);
   const i32x4 rdo = make_rsrc(dO, 2L * p.s * p.h);
   const i32x4 rl = make_rsrc(p.lse + (long)z * p.s, 4L * p.s);
+  const i32x4 rs = FULL ? rl : make_rsrc(p.lse + p.rows + (long)z * p.s, 4L * p.s);
   const i32x4 rd = make_rsrc(p.dv + (long)z * p.s, 4L * p.s);
   const int k0w = kb * 128 + 32 * wave;
   const int key = k0w + (lane & 31);
@@ -739,6 +777,7 @@ static __device__ __forceinline__ void attn_bwd_kv(const AttnArgs& p) {
     load_tile<64>(rdo, st + TILE64, wave, lane, p.h, qb * 64, p.s, dim(p));
     if (wave == 0) load_vec64(rl, st + 2 * TILE64, lane, qb * 64, p.s);
     if (wave == 1) load_vec64(rd, st + 2 * TILE64 + 1024, lane, qb * 64, p.s);
+    if (!FULL && wave == 2) load_vec64(rs, st + 2 * TILE64 + 2048, lane, qb * 64, p.s);
   };
   auto compute = [&](const char* st, int qb) {
     bwdkv_block<CAUSAL>(dk, dv, kf, vf, st, ro, to, qb * 64, k0w, key, lane, p);
@@ -775,7 +814,7 @@ static __device__ __forceinline__ void attn_bwd_kv(const AttnArgs& p) {
 // key-block kernel, which runs after this one.
 struct BwdQRows {
   bf16x8 qf[HD / 16], of[HD / 16];
-  float Lq, Dq;
+  float Lq, Sq, Dq;  // statistics (ref, ls of prob) and row term
   __device__ __forceinline__ void load_rows(const AttnArgs& p, int z, int qq, int lane) {
     const int zb = z / p.heads, zh = z % p.heads;
     const long ld = 3L * p.h;
@@ -786,6 +825,7 @@ struct BwdQRows {
     const int zb = z / p.heads, zh = z % p.heads;
     load_rows(p, z, qq, lane);
     Lq = qq < p.s ? p.lse[(long)z * p.s + qq] : 0.f;
+    Sq = !FULL && qq < p.s ? p.lse[p.rows + (long)z * p.s + qq] : 0.f;
     bf16x8 ofr[HD / 16];
     load_stationary(ofr, p.o + (long)zb * p.s * p.h + zh * dim(p), p.h, qq, p.s, lane, dim(p));
     float t = 0.f;
@@ -823,7 +863,7 @@ static __device__ __forceinline__ void bwdq_block(f32x16 (&dq)[HD / 32], const B
     zero(dp);
     two_chains<2>(sc[0], kt, j, w.qf, dp, vt, j, w.of, ro);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sc[0][r] = __builtin_amdgcn_exp2f(sc[0][r] * p.sl2 - w.Lq);
+    for (int r = 0; r < 16; ++r) sc[0][r] = prob(sc[0][r], w.Lq, w.Sq, p);
     if (need_mask) mask_scores<1>(sc, room - 32 * j, 0.f);
 #pragma unroll
     for (int r = 0; r < 16; ++r) dp[r] = sc[0][r] * (dp[r] - w.Dq);
@@ -911,9 +951,10 @@ static __device__ __forceinline__ void attn_bwd_q(const AttnArgs& p) {
 // and dO rows when it moves to qb.  The two partial sums of qb's dQ are added
 // through LDS (group 0's first).
 static __device__ __forceinline__ void attn_bwd_q_pair(const AttnArgs& p) {
-  __shared__ __attribute__((aligned(1024))) char lds[2 * FWD_GROUP + 3072];
+  __shared__ __attribute__((aligned(1024))) char lds[2 * FWD_GROUP + 1024 + VECS];
   float2* const stats = (float2*)(lds + 2 * FWD_GROUP);  // qb's (log-sum-exp, Dv) per [wave][lane]
   char* const sink = lds + 2 * FWD_GROUP + 2048;
+  float* const stats_sum = (float*)(lds + 2 * FWD_GROUP + 3072);  // the log2 sums, where they are apart
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = wave >> 2, wg = wave & 3;
@@ -939,7 +980,10 @@ static __device__ __forceinline__ void attn_bwd_q_pair(const AttnArgs& p) {
   int qq = q0 + (lane & 31);
   BwdQRows w;
   w.load(p, z, qq, lane, grp == 1 || qcur != qb);  // group 1 writes qb's Dv, group 0 qa's
-  if (grp == 1) stats[wg * 64 + lane] = make_float2(w.Lq, w.Dq);  // read after the first barrier
+  if (grp == 1) {  // read after the first barrier
+    stats[wg * 64 + lane] = make_float2(w.Lq, w.Dq);
+    if (!FULL) stats_sum[wg * 64 + lane] = w.Sq;
+  }
   RowOffs ro;
   ro.init(lane);
   TrOffs to;
@@ -977,6 +1021,7 @@ static __device__ __forceinline__ void attn_bwd_q_pair(const AttnArgs& p) {
       vm_drain();
       const float2 st2 = stats[wg * 64 + lane];
       w.Lq = st2.x;
+      if (!FULL) w.Sq = stats_sum[wg * 64 + lane];
       w.Dq = st2.y;
     }
     if (it < cnt && j + 1 == na) {
@@ -1040,7 +1085,7 @@ static __device__ __forceinline__ void attn_bwd_q_pair(const AttnArgs& p) {
 // side each, with tiles of their own: no barrier until the four partial states
 // are combined through LDS in wave order.  At that shape: forward 14.6 -> 7.2,
 // dQ 18.3 -> 8.4, dK/dV 14.7 -> 8.0 us.
-static constexpr int SPLIT_TILE = 2 * TILE64 + 2048;  // a wave's two tiles (and two row vectors)
+static constexpr int SPLIT_TILE = 2 * TILE64 + VECS;  // a wave's two tiles (and row vectors)
 
 // This wave's copies have landed; its LDS reads stay behind (no other wave
 // reads its tiles, so no barrier is needed).
@@ -1143,7 +1188,7 @@ static __device__ __forceinline__ void attn_fwd_split(const AttnArgs& p) {
   stat[lane] = make_float2(st.m_run, st.l_run + __shfl_xor(st.l_run, 32, 64));
   __syncthreads();
   float2 ml[4];
-  float m = -1e30f, l = 0.f;
+  float m = m_none(), l = 0.f;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     ml[u] = ((const float2*)(lds + u * SPLIT_TILE + 2 * TILE64))[lane];
@@ -1152,7 +1197,7 @@ static __device__ __forceinline__ void attn_fwd_split(const AttnArgs& p) {
   float a[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    a[u] = __builtin_amdgcn_exp2f(ml[u].x - m);
+    a[u] = exp_diff(ml[u].x, m, p);
     l += a[u] * ml[u].y;
   }
   bf16* const out = (bf16*)p.out + (long)zb * p.s * p.h + zh * dim(p);
@@ -1172,7 +1217,7 @@ static __device__ __forceinline__ void attn_fwd_split(const AttnArgs& p) {
       store_block(o, p.orest + (long)zb * p.s * p.h + zh * dim(p), p.h, qq, p.s, b, lane, 1.0f, dim(p));
     }
   }
-  if (wave == 0 && lane < 32 && qq < p.s) p.lse[(long)z * p.s + qq] = m + __builtin_amdgcn_logf(l);
+  if (wave == 0 && lane < 32 && qq < p.s) store_stats(p, (long)z * p.s + qq, m, l);
 }
 
 template <bool CAUSAL>
@@ -1244,6 +1289,7 @@ static __device__ __forceinline__ void attn_bwd_kv_split(const AttnArgs& p) {
   const i32x4 rq = make_rsrc(Q, 2L * p.s * ld);
   const i32x4 rdo = make_rsrc(dO, 2L * p.s * p.h);
   const i32x4 rl = make_rsrc(p.lse + (long)z * p.s, 4L * p.s);
+  const i32x4 rs = FULL ? rl : make_rsrc(p.lse + p.rows + (long)z * p.s, 4L * p.s);
   const i32x4 rd = make_rsrc(p.dv + (long)z * p.s, 4L * p.s);
   const int k0w = blk * 32, key = k0w + (lane & 31);
   const int nqb = (p.s + 63) / 64;
@@ -1253,6 +1299,7 @@ static __device__ __forceinline__ void attn_bwd_kv_split(const AttnArgs& p) {
     load_tile_own(rdo, area + TILE64, lane, p.h, qb * 64, p.s, dim(p));
     load_vec64(rl, area + 2 * TILE64, lane, qb * 64, p.s);
     load_vec64(rd, area + 2 * TILE64 + 1024, lane, qb * 64, p.s);
+    if (!FULL) load_vec64(rs, area + 2 * TILE64 + 2048, lane, qb * 64, p.s);
   };
   if (first < nqb) issue(first);
   bf16x8 kf[HD / 16], vf[HD / 16];

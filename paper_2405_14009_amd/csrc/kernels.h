@@ -61,10 +61,12 @@ hipError_t softmax_backward(int elt, const float* dP, const void* P, void* dS, l
 // O = softmax(Q K^T / sqrt(d), causal) V without materialising the scores.
 // qkv: [b*s, 3h] with column blocks Q | K | V (head j at columns j*d of each);
 // o: [b*s, h]; lse: [b, heads, s] fp32 base-2 log-sum-exp of the scaled scores
-// (written by the forward, read by the backward).  The backward writes dQ, dK,
+// (written by the forward, read by the backward), two such arrays for narrow
+// heads (attn_flash_narrow): a reference score per row, and log2 of the sum
+// relative to it.  The backward writes dQ, dK,
 // dV into the three column blocks of dqkv [b*s, 3h]; dv_scratch holds b*heads*s
 // floats.  h == heads * d.  orest [b*s, h] (written by the forward, read by the
-// backward; unused where attn_flash_keeps_rest says no): what the bf16 rounding
+// backward; narrow heads only): what the bf16 rounding
 // of o drops.  Head dimensions other than 128 take it for
 // sequences of more than one query block (128); up to that the materialised
 // kernels stay, whose probabilities are small there, as stages of short
@@ -75,7 +77,7 @@ bool attn_flash_supported(int elt, int head_dim, int s);
 // the current device, rather than one workgroup per query block; also true for
 // grids so small that the waves of a workgroup share a block's keys.
 bool attn_flash_paired(int b, int s, int heads, int head_dim);
-bool attn_flash_keeps_rest(int head_dim);
+bool attn_flash_narrow(int head_dim);  // of the supported ones: not 128
 hipError_t attn_flash_forward(const void* qkv, void* o, void* orest, float* lse, int b, int s, int heads, int h,
                               int causal, hipStream_t st);
 hipError_t attn_flash_backward(const void* qkv, const void* o, const void* orest, const void* dout,

@@ -64,7 +64,7 @@ struct FLayer {
   // Dg: gelu'(U) of the FFN, which the FC2 input gradient multiplies by (the
   // forward stores it instead of U: the same information for B_input, and the
   // derivative is formed where the fp32 U is at hand).  P: attention
-  // probabilities, or the row log-sum-exp (fused attention).  Or: what the
+  // probabilities, or the row statistics (fused attention).  Or: what the
   // bf16 rounding of O drops (fused attention below head dimension 128).
   size_t QKV, Dg, P, Or, bytes;
 };
@@ -213,8 +213,9 @@ rc_status make_layout(const rc_stage_config* c, Layout& y) {
   const size_t rows = (size_t)y.b * y.a * y.s;
   y.fl.QKV = take(T * 3 * h * E);
   y.fl.Dg = take(T * f * E);
-  y.fl.P = take(y.flash ? rows * 4 : ss * E);
-  y.fl.Or = take(y.flash && attn_flash_keeps_rest(d) ? T * h * E : 0);
+  const bool narrow = y.flash && attn_flash_narrow(d);
+  y.fl.P = take(y.flash ? rows * (narrow ? 8 : 4) : ss * E);
+  y.fl.Or = take(narrow ? T * h * E : 0);
   y.fl.bytes = o;
   y.wslot_bytes = (size_t)y.L * w.bytes;
   y.fslot_bytes = (size_t)y.L * y.fl.bytes;

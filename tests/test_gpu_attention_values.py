@@ -67,3 +67,28 @@ def test_common_component_of_values(form, d):
     assert e < bound, (e, bound)
     for mb in o.y:
         assert rel_l2(g.y[mb], o.y[mb]) < 2e-2 and rel_l2(g.dx[mb], o.dx[mb]) < 2e-2
+
+
+@pytest.mark.parametrize("scale", [2.0 ** 10, -2.0 ** 52])
+@pytest.mark.parametrize("form", list(FORMS))
+def test_scores_of_any_size(form, scale):
+    """Queries and keys that are one constant each (weights zero, biases exact
+    in bf16), so that every key of a row has the same score, 8 scale^2 after the
+    scaling at d = 64, and the softmax is uniform whatever that score is.  Scores
+    of 8e6, which fp32 holds to one part in 2^24 only, and of -1.6e32, whose
+    exponentials have no range: the output, the input gradient and the value
+    weights' gradient (dV = P^T dO) stay within the bar of bf16 stages."""
+    cfg = narrow(form, 64)
+    h = cfg.hidden
+    params = gen_params(cfg)
+    params[0][2][:, :2 * h] = 0
+    params[0][3][:h] = abs(scale)
+    params[0][3][h:2 * h] = scale
+    log(f"[values] {form} h={h} s={cfg.seq} b={cfg.micro_batch}: queries and keys of {scale:.1e}")
+    g = run_gpu(cfg, params=params)
+    o = oracle.run_oplist(cfg, params=params)
+    e = {"grad": rel_l2(g.grads[0][2][:, 2 * h:], o.grads[0][2][:, 2 * h:])}
+    for mb in o.y:
+        e["y"], e["dx"] = rel_l2(g.y[mb], o.y[mb]), rel_l2(g.dx[mb], o.dx[mb])
+    log(f"[values] {form} {scale:.1e}: rel-L2 of the value weights' gradient, y, dx {e}")
+    assert all(v < 2e-2 for v in e.values()), e
