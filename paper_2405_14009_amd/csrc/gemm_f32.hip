@@ -307,6 +307,12 @@ hipError_t launch_tiles(const GemmParams& p, const F32Plan& pl, int y, hipStream
 template <bool AK, bool BKC, int EPI>
 hipError_t launch(const GemmParams& p, const F32Plan& pl, hipStream_t s) {
   GemmParams q = p;
+  if (f32_wide(p.lda, p.ldb)) {
+    q.splits = 1;
+    const dim3 grid((unsigned)(((p.M + 31L) / 32) * ((p.N + 31L) / 32)), (unsigned)(p.batch * p.heads));
+    hipLaunchKernelGGL((gemm_small_kernel<float, AK, BKC, EPI, true>), grid, dim3(256), 0, s, q);
+    return hipGetLastError();
+  }
   q.splits = pl.splits;
   if (pl.splits == 1) return launch_tiles<AK, BKC, EPI>(q, pl, p.batch * p.heads, s);
   q.split_k = pl.split_k;

@@ -89,6 +89,12 @@ inline GemmPlan plan_bf16(long M, long N, long K, bool tn, long z, long room_flo
   return best;
 }
 
+// Whether an operand of a 128-row tile spans more bytes than the 2^31 that the
+// fp32 kernels' buffer offsets reach (tiles start at their own 64-bit address, so
+// only the rows of one tile count).  The 32x32 kernel then copies through
+// registers; such a stage is bound by its state of tens of GB, not by this.
+inline bool f32_wide(long lda, long ldb) { return 127L * 4 * std::max(lda, ldb) + 512 > 0x7fffffffL; }
+
 struct F32Plan {
   int bm;               // tiles of bm x bm: 32, 64 or 128
   long tiles;

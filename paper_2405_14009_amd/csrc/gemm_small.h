@@ -14,6 +14,10 @@
 // contiguous bytes).  m/n-contiguous fp32: 128 bytes per k-row, k-row k at row
 // k ^ (k / 4 % 2), so that the two half-waves, 4 k-rows apart, use different
 // banks.
+//
+// WIDE: matrices whose 32-row panels span more than the 2^31 bytes that a buffer
+// offset reaches (fp32 only; bf16 stages refuse them).  The copies then are
+// loads from 64-bit addresses, stored to the same places of the ring.
 #pragma once
 
 #include "gemm.h"
@@ -42,6 +46,16 @@ struct SmallOperand {
     const bool ok = mn0 + mn < MN && k0 + k < kend;
     const uint32_t off = ok ? (uint32_t)(KC ? mn * ld + k : k * ld + mn) * (uint32_t)sizeof(E) : kOOB;
     dma16(rs, __builtin_amdgcn_readfirstlane(lds_addr(tile) + q * 1024), off);
+  }
+  // the same slice through registers, from p (the matrix at mn0 and k0)
+  __device__ __forceinline__ static void copy(const E* p, char* tile, long ld, int mn0, int MN, int k0, int kend,
+                                              int lane, int q) {
+    const int r = RPS * q + lane / CPR;
+    const int mn = KC ? r : EPC * (lane % CPR);
+    const int k = KC ? EPC * ((lane % CPR) ^ ((r >> 1) & 7)) : sizeof(E) == 4 ? r ^ ((r >> 2) & 1) : r;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (mn0 + mn < MN && k0 + k < kend) v = *(const uint4*)(p + (KC ? mn * ld + k : k * ld + mn));
+    *(uint4*)(tile + q * 1024 + lane * 16) = v;
   }
   __device__ __forceinline__ static const E* at(const E* p, long ld, int mn0, int k0) {
     return KC ? p + (long)mn0 * ld + k0 : p + (long)k0 * ld + mn0;
@@ -100,7 +114,7 @@ __device__ __forceinline__ void small_products(f32x16 (&acc)[2], const float4 (&
   }
 }
 
-template <class E, bool AK, bool BKC, int EPI>
+template <class E, bool AK, bool BKC, int EPI, bool WIDE = false>
 __global__ __launch_bounds__(256) void gemm_small_kernel(GemmParams p) {
   typedef SmallOperand<E, AK> OpA;
   typedef SmallOperand<E, BKC> OpB;
@@ -154,11 +168,18 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmParams p) {
     at();
   }
   auto issue = [&](char* st) {
-    const i32x4 ra = make_rsrc(pa, 0x7fffffffL), rb = make_rsrc(pb, 0x7fffffffL);
+    if constexpr (WIDE) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) OpA::issue(ra, st, p.lda, m0, p.M, k0, kend, lane, q);
+      for (int q = 0; q < 4; ++q) OpA::copy(pa, st, p.lda, m0, p.M, k0, kend, lane, q);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) OpB::issue(rb, st + 4096, p.ldb, n0, p.N, k0, kend, lane, q);
+      for (int q = 0; q < 4; ++q) OpB::copy(pb, st + 4096, p.ldb, n0, p.N, k0, kend, lane, q);
+    } else {
+      const i32x4 ra = make_rsrc(pa, 0x7fffffffL), rb = make_rsrc(pb, 0x7fffffffL);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) OpA::issue(ra, st, p.lda, m0, p.M, k0, kend, lane, q);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) OpB::issue(rb, st + 4096, p.ldb, n0, p.N, k0, kend, lane, q);
+    }
     k0 += 4 * BK;
     pa += 4 * OpA::step(p.lda);
     pb += 4 * OpB::step(p.ldb);

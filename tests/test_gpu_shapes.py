@@ -113,3 +113,36 @@ def test_split_products_are_reproducible():
         assert np.array_equal(a.y[mb], b.y[mb]) and np.array_equal(a.dx[mb], b.dx[mb])
     for p in range(12):
         assert np.array_equal(a.grads[0][p], b.grads[0][p]), p
+
+
+def test_f32_rows_beyond_buffer_offsets():
+    """An fp32 stage whose FFN rows are so wide (8 600 000) that the last of a
+    tile's 64 token rows starts 2^31 bytes past its first.  The FFN's weights are
+    zero but for 64 columns spread over it, where gelu(0) = 0 leaves the same
+    stage as one of 64 FFN columns, which the oracle runs."""
+    from paper_2405_14009_amd import RC_READ_GRAD, Stage
+    from synth import MB, gen_params
+    from synth.schedules import Op
+    import numpy as np
+    f = 8600000
+    cfg = get_config("small_f32").with_(layers=1, hidden=64, heads=1, ffn=64, seq=64, micro_batch=1, n_mb=1, rerouted=())
+    log(f"[shape] f32 h=64 s=64 f={f}")
+    at = np.linspace(0, f - 1, 64).astype(np.int64)
+    params = gen_params(cfg)
+    wide = list(params[0])
+    wide[8], wide[9], wide[10] = (np.zeros(n, np.float32) for n in ((64, f), (f,), (f, 64)))
+    wide[8][:, at], wide[9][at], wide[10][at] = params[0][8], params[0][9], params[0][10]
+    stage = Stage.from_config(cfg.with_(ffn=f))
+    stage.load_params([wide])
+    del wide
+    mb = MB(0, 0)
+    g = run_gpu(cfg, [Op("F", mb), Op("B", mb), Op("W", mb)], stage=stage, read_state=False)
+    o = oracle.run_oplist(cfg, [Op("F", mb), Op("B", mb), Op("W", mb)], params=params)
+    grads = [stage.read(RC_READ_GRAD, 0, p) for p in range(12)]
+    stage.close()
+    assert not np.any(np.delete(grads[9], at))
+    grads[8], grads[9], grads[10] = grads[8][:, at], grads[9][at], grads[10][at]
+    key = tuple(mb)
+    log(f"[shape] f={f}: y {rel_l2(g.y[key], o.y[key]):.2e} dx {rel_l2(g.dx[key], o.dx[key]):.2e}")
+    assert rel_l2(g.y[key], o.y[key]) < 1e-5 and rel_l2(g.dx[key], o.dx[key]) < 1e-5
+    log(f"[shape] f={f}: worst gradient rel-L2 {compare_grads(cfg, [grads], o.grads, 1e-5):.2e}")
