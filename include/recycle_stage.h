@@ -356,13 +356,12 @@ rc_status rc_stage_profile_read(rc_stage* st, rc_kernel_stat* out);
  *                         128 queries (non-causal, or causal unless paired);
  *   RC_ATTN_PAIRED        fused causal, one workgroup per pair of query
  *                         blocks (q, last - q) of equal total length (grids
- *                         that fill the compute units once).
- * (Grids of at most one workgroup of 32 queries per compute unit, two for
- * head_dim <= 64, run the fused kernels' form for small grids, whose waves
- * share a block's keys: reported as RC_ATTN_PAIRED if causal, else
- * RC_ATTN_BLOCK.)
+ *                         that fill the compute units once);
+ *   RC_ATTN_SPLIT         fused, one workgroup per 32 queries, whose four waves
+ *                         share their keys (grids of at most one such workgroup
+ *                         per compute unit, two for head_dim <= 64).
  * Host only; works on dry-run handles.  Errors: RC_ERR_INVALID_ARG. */
-enum { RC_ATTN_MATERIALISED = 0, RC_ATTN_BLOCK = 1, RC_ATTN_PAIRED = 2 };
+enum { RC_ATTN_MATERIALISED = 0, RC_ATTN_BLOCK = 1, RC_ATTN_PAIRED = 2, RC_ATTN_SPLIT = 3 };
 rc_status rc_stage_attention_kernels(rc_stage* st, int32_t* kind);
 
 /* Wait for the handle's stream; reports any deferred device error as RC_ERR_HIP. */

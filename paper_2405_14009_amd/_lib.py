@@ -16,7 +16,7 @@ RC_FP32, RC_BF16 = 0, 1
 RC_OP_F, RC_OP_B, RC_OP_W, RC_OP_STEP, RC_OP_SKIP, RC_OP_ROLLBACK = 0, 1, 2, 3, 4, 5
 RC_READ_PARAM, RC_READ_GRAD, RC_READ_ADAM_M, RC_READ_ADAM_V = 0, 1, 2, 3
 RC_NUM_PARAMS = 12
-RC_ATTN_MATERIALISED, RC_ATTN_BLOCK, RC_ATTN_PAIRED = 0, 1, 2
+RC_ATTN_MATERIALISED, RC_ATTN_BLOCK, RC_ATTN_PAIRED, RC_ATTN_SPLIT = 0, 1, 2, 3
 RC_STATIC_WORK_BYTES = 96 * 1024 * 1024
 
 # Every symbol the header declares, for load checks.

@@ -5,18 +5,12 @@
 #include <hip/hip_runtime.h>
 
 #include "common.h"
-
-// Whether a grid takes the kernels of small grids: no more workgroups of 32
-// rows than compute units hold at once (the tiles of a head of up to 64
-// columns let two share a CU).
-inline bool attn_split_grid(int s, int bh, int head_dim) {
-  return (long)((s + 31) / 32) * bh <= (head_dim <= 64 ? 2L : 1L) * device_compute_units();
-}
+#include "kernels.h"
 
 struct AttnArgs;
-#define ATTN_FLASH_DECL(NAME)                                                              \
-  hipError_t attn_fwd_##NAME(const AttnArgs& a, int causal, bool paired, hipStream_t st); \
-  hipError_t attn_bwd_##NAME(const AttnArgs& a, int causal, bool paired, hipStream_t st);
+#define ATTN_FLASH_DECL(NAME)                                                               \
+  hipError_t attn_fwd_##NAME(const AttnArgs& a, int causal, AttnForm form, hipStream_t st); \
+  hipError_t attn_bwd_##NAME(const AttnArgs& a, int causal, AttnForm form, hipStream_t st);
 ATTN_FLASH_DECL(32)
 ATTN_FLASH_DECL(64)
 ATTN_FLASH_DECL(96)

@@ -38,7 +38,14 @@ bool pair_grid_fills(long wgs) {
   return wgs <= cus && 10 * wgs >= 9 * cus;
 }
 
-typedef hipError_t (*Launch)(const AttnArgs&, int, bool, hipStream_t);
+// Whether a grid takes the kernels of small grids: no more workgroups of 32
+// rows than compute units hold at once (the tiles of a head of up to 64
+// columns let two share a CU).
+bool split_grid(int s, int bh, int head_dim) {
+  return (long)((s + 31) / 32) * bh <= (head_dim <= 64 ? 2L : 1L) * device_compute_units();
+}
+
+typedef hipError_t (*Launch)(const AttnArgs&, int, AttnForm, hipStream_t);
 // The kernels of the fewest compiled columns that hold the head.
 Launch fwd_of(int d) {
   if (d == 128) return attn_fwd_128_full;
@@ -60,9 +67,10 @@ bool attn_flash_supported(int elt, int head_dim, int s) {
   return head_dim == 128 || s > 128;
 }
 
-bool attn_flash_paired(int b, int s, int heads, int head_dim) {
+AttnForm attn_flash_form(int b, int s, int heads, int head_dim, int causal) {
   const int nqb = (s + 127) / 128;
-  return attn_split_grid(s, b * heads, head_dim) || pair_grid_fills((long)((nqb + 1) / 2) * b * heads);
+  if (split_grid(s, b * heads, head_dim)) return ATTN_SPLIT;
+  return causal && pair_grid_fills((long)((nqb + 1) / 2) * b * heads) ? ATTN_PAIRED : ATTN_BLOCK;
 }
 
 bool attn_flash_narrow(int head_dim) { return head_dim != 128; }
@@ -75,7 +83,7 @@ hipError_t attn_flash_forward(const void* qkv, void* o, void* orest, float* lse,
   a.out = (bf16*)o;
   a.orest = (bf16*)orest;
   a.lse = lse;
-  return fwd_of(a.d)(a, causal, attn_flash_paired(b, s, heads, a.d), st);
+  return fwd_of(a.d)(a, causal, attn_flash_form(b, s, heads, a.d, causal), st);
 }
 
 hipError_t attn_flash_backward(const void* qkv, const void* o, const void* orest, const void* dout,
@@ -90,5 +98,5 @@ hipError_t attn_flash_backward(const void* qkv, const void* o, const void* orest
   a.out = (bf16*)dqkv;
   a.lse = (float*)lse;
   a.dv = dv_scratch;
-  return bwd_of(a.d)(a, causal, attn_flash_paired(b, s, heads, a.d), st);
+  return bwd_of(a.d)(a, causal, attn_flash_form(b, s, heads, a.d, causal), st);
 }

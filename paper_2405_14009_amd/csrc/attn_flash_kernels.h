@@ -1384,11 +1384,11 @@ __global__ __launch_bounds__(256) void attn_bwd_kv_split_k(AttnArgs p) {
 }
 
 template <int HD, bool FULL>
-hipError_t attn_fwd_launch(const AttnArgs& a, int causal, bool paired, hipStream_t st) {
+hipError_t attn_fwd_launch(const AttnArgs& a, int causal, AttnForm form, hipStream_t st) {
   const int nqb = (a.s + 127) / 128;
   const long pairs = (long)((nqb + 1) / 2) * a.bh;
   const dim3 grid((unsigned)(nqb * (long)a.bh));
-  if (attn_split_grid(a.s, a.bh, a.d)) {
+  if (form == ATTN_SPLIT) {
     const dim3 g((unsigned)(((a.s + 31) / 32) * (long)a.bh));
     if (causal)
       hipLaunchKernelGGL((attn_fwd_split_k<HD, FULL, true>), g, dim3(256), 0, st, a);
@@ -1396,7 +1396,7 @@ hipError_t attn_fwd_launch(const AttnArgs& a, int causal, bool paired, hipStream
       hipLaunchKernelGGL((attn_fwd_split_k<HD, FULL, false>), g, dim3(256), 0, st, a);
     return hipGetLastError();
   }
-  if (causal && paired)
+  if (form == ATTN_PAIRED)
     hipLaunchKernelGGL((attn_fwd_pair_k<HD, FULL>), dim3((unsigned)pairs), dim3(512), 0, st, a);
   else if (causal)
     hipLaunchKernelGGL((attn_fwd_k<HD, FULL, true>), grid, dim3(256), 0, st, a);
@@ -1407,11 +1407,11 @@ hipError_t attn_fwd_launch(const AttnArgs& a, int causal, bool paired, hipStream
 
 // the query-block kernel also writes Dv, which the key-block kernel reads
 template <int HD, bool FULL>
-hipError_t attn_bwd_launch(const AttnArgs& a, int causal, bool paired, hipStream_t st) {
+hipError_t attn_bwd_launch(const AttnArgs& a, int causal, AttnForm form, hipStream_t st) {
   const int nqb = (a.s + 127) / 128;
   const long pairs = (long)((nqb + 1) / 2) * a.bh;
   const dim3 grid((unsigned)(nqb * (long)a.bh));
-  if (attn_split_grid(a.s, a.bh, a.d)) {
+  if (form == ATTN_SPLIT) {
     const dim3 g((unsigned)(((a.s + 31) / 32) * (long)a.bh));
     if (causal) {
       hipLaunchKernelGGL((attn_bwd_q_split_k<HD, FULL, true>), g, dim3(256), 0, st, a);
@@ -1422,7 +1422,7 @@ hipError_t attn_bwd_launch(const AttnArgs& a, int causal, bool paired, hipStream
     }
     return hipGetLastError();
   }
-  if (causal && paired)
+  if (form == ATTN_PAIRED)
     hipLaunchKernelGGL((attn_bwd_q_pair_k<HD, FULL>), dim3((unsigned)pairs), dim3(512), 0, st, a);
   else if (causal)
     hipLaunchKernelGGL((attn_bwd_q_k<HD, FULL, true>), grid, dim3(256), 0, st, a);

@@ -72,11 +72,11 @@ hipError_t softmax_backward(int elt, const float* dP, const void* P, void* dS, l
 // kernels stay, whose probabilities are small there, as stages of short
 // sequences and narrow heads report through rc_stage_attention_kernels.
 bool attn_flash_supported(int elt, int head_dim, int s);
-// Whether causal fused attention over b sequences of s tokens and `heads`
-// heads runs the paired kernels (one workgroup per pair of query blocks) on
-// the current device, rather than one workgroup per query block; also true for
-// grids so small that the waves of a workgroup share a block's keys.
-bool attn_flash_paired(int b, int s, int heads, int head_dim);
+// The kernels that fused attention over b sequences of s tokens and `heads`
+// heads runs on the current device: one workgroup per query block, per pair of
+// query blocks (causal), or per 32 queries, whose waves share their keys.
+enum AttnForm { ATTN_BLOCK, ATTN_PAIRED, ATTN_SPLIT };
+AttnForm attn_flash_form(int b, int s, int heads, int head_dim, int causal);
 bool attn_flash_narrow(int head_dim);  // of the supported ones: not 128
 hipError_t attn_flash_forward(const void* qkv, void* o, void* orest, float* lse, int b, int s, int heads, int h,
                               int causal, hipStream_t st);

@@ -1148,8 +1148,11 @@ rc_status rc_stage_set_stream(rc_stage* st, void* hip_stream) {
 rc_status rc_stage_attention_kernels(rc_stage* st, int32_t* kind) {
   if (!st || !kind) return fail(RC_ERR_INVALID_ARG, "null argument");
   const Layout& y = st->lay;
-  if (!y.flash) *kind = RC_ATTN_MATERIALISED;
-  else *kind = y.causal && attn_flash_paired(y.b, y.s, y.a, y.d) ? RC_ATTN_PAIRED : RC_ATTN_BLOCK;
+  const AttnForm form = attn_flash_form(y.b, y.s, y.a, y.d, y.causal);
+  *kind = !y.flash ? RC_ATTN_MATERIALISED
+          : form == ATTN_SPLIT ? RC_ATTN_SPLIT
+          : form == ATTN_PAIRED ? RC_ATTN_PAIRED
+                                : RC_ATTN_BLOCK;
   return RC_OK;
 }
 

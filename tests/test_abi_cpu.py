@@ -129,10 +129,18 @@ def test_attention_kernel_query_on_dry_run_handles():
     kw = dict(num_layers=1, ffn=256, micro_batch=1, dry_run=True)
     assert Stage(hidden=256, heads=4, seq_len=128, dtype="f32", **kw).attention_kernels() == "materialised"
     assert Stage(hidden=256, heads=4, seq_len=128, dtype="bf16", **kw).attention_kernels() == "materialised"
-    assert Stage(hidden=256, heads=2, seq_len=128, dtype="bf16", causal=False,
-                 **kw).attention_kernels() == "block"
-    # a small causal grid (one workgroup per compute unit at most) takes the paired kernels
-    assert Stage(hidden=256, heads=2, seq_len=128, dtype="bf16", **kw).attention_kernels() == "paired"
+    # a small grid (at most one workgroup of 32 queries per compute unit, two for narrow heads)
+    for causal in (True, False):
+        assert Stage(hidden=256, heads=2, seq_len=128, dtype="bf16", causal=causal, **kw).attention_kernels() == "split"
+        for heads, d, seq, kind in ((4, 128, 2048, "split"), (8, 64, 2048, "split"), (8, 64, 2056, "block")):
+            assert Stage(hidden=heads * d, heads=heads, seq_len=seq, dtype="bf16", causal=causal,
+                         **kw).attention_kernels() == kind, (heads, d, seq, causal)
+    # 256 pairs of query blocks: one per compute unit; 96 heads of 8 pairs: three rounds
+    kw["ffn"] = 64
+    for heads, seq, causal, kind in ((32, 2048, True, "paired"), (32, 2048, False, "block"), (40, 2048, True, "block"),
+                                     (96, 2048, True, "block"), (30, 2048, True, "paired")):
+        assert Stage(hidden=128 * heads, heads=heads, seq_len=seq, dtype="bf16", causal=causal,
+                     **kw).attention_kernels() == kind, (heads, seq, causal)
 
 
 def test_bf16_state_holds_weight_copies():
