@@ -47,9 +47,6 @@ inline double split_us(int splits, long M, long N) {
 // parallelism with operand traffic.  The constants are fits (us) to launches
 // of each kernel alone on the card, M and N 384 .. 16384, K 384 .. 32768:
 // within 10 % where a kernel is the best choice, 30 % elsewhere.
-// (256x128 forward and input-gradient tiles: 0.94 a k-tile as in a stage's
-// iteration, 0.97 alone.  2048x12288x4096 then keeps them instead of 1.5 rounds of
-// 256x256: the 6.7B iteration 39.18 -> 39.04 ms, coupled 5.183 -> 5.167.)
 // room_floats: split workspace; colsum_floats: what colsum_rows may take (< 0:
 // no column sums).  256x256 tiles unsplit always qualify.
 inline GemmPlan plan_bf16(long M, long N, long K, bool tn, long z, long room_floats, long colsum_floats, int cus) {
@@ -60,7 +57,7 @@ inline GemmPlan plan_bf16(long M, long N, long K, bool tn, long z, long room_flo
   };
   const Kind kinds[6] = {
       {TILE_256, 256, 256, {14.0, 10.0, 1.09, 1.50, false}},
-      {TILE_256x128, 256, 128, {9.8, 2.5, tn ? 0.76 : 0.61, tn ? 1.00 : 0.94, false}},
+      {TILE_256x128, 256, 128, {9.8, 2.5, tn ? 0.76 : 0.61, tn ? 1.00 : 0.97, false}},
       {TILE_128, 128, 128, {7.5, 0.0, 0.62, 0.68, true}},
       {TILE_64, 64, 64, {4.0, 0.0, 0.25, 0.28, true}},
       {TILE_32, 32, 32, {3.6, 2.4, 0.07, 0.10, false}},
