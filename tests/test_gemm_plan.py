@@ -51,12 +51,55 @@ int main() {
 """
 
 
-def test_plans_cover_and_fit(tmp_path):
+def compiled(tmp_path, main):
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     src = tmp_path / "plan.cpp"
-    src.write_text(MAIN)
+    src.write_text(main)
     exe = tmp_path / "plan"
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    return str(exe)
+
+
+def test_plans_cover_and_fit(tmp_path):
+    r = subprocess.run([compiled(tmp_path, MAIN)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
+
+
+# Unsplit products as timed alone on the card (us): weight-gradient layout or
+# not, M, N, K, then 256x256, 256x128, 128x128, 64x64 and 192x256 tiles (0: not
+# timed).  Partial rounds of large tiles, second rounds of tiles that share a
+# compute unit, short and long reductions.
+TIMED = [
+    (0, 2048, 12288, 12288, (553, 508, 673, 0, 714)), (0, 2048, 12288, 36864, (1691, 1570, 0, 0, 2366)),
+    (0, 2048, 36864, 12288, (1475, 1565, 0, 0, 1762)), (0, 2048, 20480, 5120, (377, 391, 485, 0, 424)),
+    (0, 2048, 10240, 2048, (106, 100, 119, 186, 95)), (0, 4096, 1280, 5120, (118, 75, 92, 120, 105)),
+    (0, 4096, 2048, 4096, (95, 63, 82, 151, 82)), (0, 4096, 3072, 4096, (97, 114, 157, 227, 145)),
+    (0, 2048, 2560, 2560, (56, 36, 39, 59, 44)), (0, 512, 1024, 1024, (25, 18, 15, 8, 21)),
+    (0, 2048, 4096, 16384, (355, 224, 314, 0, 316)),
+    (1, 8192, 32768, 512, (652, 911, 719, 0, 0)), (1, 4096, 16384, 512, (143, 199, 164, 245, 0)),
+    (1, 49152, 12288, 512, (1269, 1681, 1432, 0, 0)), (1, 1536, 6144, 4096, (107, 128, 116, 180, 0)),
+    (1, 3072, 3072, 2048, (53, 75, 65, 96, 0)), (1, 1024, 4096, 4096, (84, 65, 53, 67, 0)),
+    (1, 4096, 2560, 4096, (110, 129, 138, 209, 0)), (1, 12288, 12288, 2048, (643, 773, 860, 0, 0)),
+]
+
+
+def test_choice_on_timed_products(tmp_path):
+    """Without split workspace the choice is within 6 % of the fastest tile."""
+    exe = compiled(tmp_path, """
+#include <cstdio>
+#include "gemm_plan.h"
+int main() {
+  int tn;
+  long M, N, K;
+  while (std::scanf("%d %ld %ld %ld", &tn, &M, &N, &K) == 4) std::printf("%d\\n", (int)plan_bf16(M, N, K, tn, 1, 0, -1, 256).tile);
+}
+""")
+    text = "".join("%d %d %d %d\n" % row[:4] for row in TIMED)
+    out = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=60, check=True).stdout.split()
+    bad = []
+    for row, tile in zip(TIMED, map(int, out)):
+        us = row[4][{0: 0, 1: 1, 2: 2, 3: 3, 5: 4}[tile]]
+        if not us or us > 1.06 * min(u for u in row[4] if u):
+            bad.append((row, tile))
+    assert len(out) == len(TIMED) and not bad, bad
