@@ -625,6 +625,7 @@ rc_status run_backward_weight(rc_stage* st, const int* ws, int n) {
   hipStream_t s = st->stream;
   float* part = (float*)(st->work + y.off_part);
   float* grads = (float*)(st->state + y.off_grad);
+  const double rb = acc ? 8.0 : 4.0;  // bytes of an element's gradient update
   for (int l = 0; l < y.L; ++l) {
     ColSegs sg;
     sg.base = st->stash + (size_t)l * y.w.bytes;
@@ -657,15 +658,16 @@ rc_status run_backward_weight(rc_stage* st, const int* ws, int n) {
       if (!y.bf) continue;
       bias[nbias++] = {g.colsum_work, rows, (int)N, gradp(st, l, q.bpid)};
       if (y.cs_shared) {
+        Prof pb(st, RC_K_REDUCE, 0, rb * N);
         HIPCHK(colsum(E, sg, n, T, nullptr, 0, bias, nbias, acc, nullptr, 0, s));
         nbias = 0;
       }
     }
-    // Column sums (bytes: n micro-batches' inputs, then the gradient update).
-    const double rb = acc ? 8.0 : 4.0;
-    const double bias_in = y.bf ? 0.0 : (double)T * (6 * h + f) * E;
+    // Column sums (bytes: n micro-batches' inputs, then the gradient update; the
+    // partial bias sums of the products are no input of the layer's).
+    const double bias_in = y.bf ? 0.0 : (double)T * (5 * h + f) * E;
     Prof pr(st, RC_K_REDUCE, 0,
-            n * (bias_in + 4.0 * T * h * E + 16.0 * T) + (y.bf ? 0.0 : rb * (6 * h + f)) + 4 * rb * h);
+            n * (bias_in + 4.0 * T * h * E + 16.0 * T) + (y.cs_shared ? 0.0 : rb * (5 * h + f)) + 4 * rb * h);
     ColJob jobs[COLSUM_MAX_JOBS];
     const int njobs = reductions(y, l, grads, jobs);
     HIPCHK(colsum(E, sg, n, T, jobs, njobs, bias, nbias, acc, part, y.part_floats, s));

@@ -253,3 +253,24 @@ def test_simulated_peer_op_list_drives_the_stage():
     assert st.op_log() == [tuple(r) for r in o.stage.log]
     log(f"[simulated peer] {len(mine)} ops, {rep.weight_calls} weight-pass calls")
     st.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_profiled_reduction_bytes(dtype):
+    """The column sums' class counts each input once (the LayerNorm operands and
+    statistics, and on fp32 stages the output gradients; the bf16 products have
+    already summed those) and the LayerNorm and bias gradients."""
+    from paper_2405_14009_amd import Stage
+    from synth.schedules import Op
+    cfg = get_config("small_bf16").with_(dtype=dtype, layers=2, n_mb=2, rerouted=())
+    stage = Stage.from_config(cfg)
+    stage.load_params(gen_params(cfg))
+    run_gpu(cfg, [Op("F", MB(0, 0)), Op("B", MB(0, 0))], stage=stage, read_state=False)
+    stage.profile_enable(True)
+    stage.backward_weight(MB(0, 0))
+    got = stage.profile_read()["reduce"]
+    stage.close()
+    T, h, f, e = cfg.tokens, cfg.hidden, cfg.ffn, 2 if dtype == "bf16" else 4
+    want = 4 * T * h * e + 16 * T + (T * (5 * h + f) * e if dtype == "f32" else 0) + 4 * (4 * h + 5 * h + f)
+    log(f"[profile] {dtype}: reductions {got}")
+    assert got["launches"] == cfg.layers and got["bytes"] == cfg.layers * want and got["ms"] > 0
