@@ -106,10 +106,10 @@ TEST_CONFIGS = {
         causal=True, dtype="f32", n_mb=3, rerouted=(2,), schedule="1f1b_deferred_shuffled_w",
         warmup=2, perturbed=True),
     # A wide FFN makes the FC1 forward, FC2 input-gradient and FC1/FC2 weight
-    # products large enough to take 256 x 256 GEMM tiles, with ragged edges
-    # (640 tokens = 2.5 tiles, hidden 1152 = 4.5 tiles).
+    # products large enough to take 256 x 256 GEMM tiles on a 256-CU device, with
+    # ragged edges (1800 tokens = 7.03 tiles, hidden 1152 = 4.5, ffn 8008 = 31.3).
     "wide_bf16": StageConfig(
-        name="wide_bf16", layers=1, hidden=1152, heads=9, ffn=12288, seq=320, micro_batch=2,
+        name="wide_bf16", layers=1, hidden=1152, heads=9, ffn=8008, seq=600, micro_batch=3,
         causal=True, dtype="bf16", n_mb=2, rerouted=(1,), schedule="1f1b_deferred_shuffled_w",
         warmup=2, perturbed=True),
     # Causal attention whose grid of query-block pairs (4 sequences x 10 heads
@@ -120,11 +120,12 @@ TEST_CONFIGS = {
         name="block_bf16", layers=1, hidden=1280, heads=10, ffn=2048, seq=1024, micro_batch=4,
         causal=True, dtype="bf16", n_mb=2, rerouted=(1,), schedule="1f1b_deferred_shuffled_w",
         warmup=2, perturbed=True),
-    # Weight-gradient products of more than one round of 256 x 256 tiles with
-    # ragged edges (FC1: [1152, 16200] = 5 x 64 tiles, FC2: 64 x 5), which the
-    # launcher gives to the persistent kernel on a 256-CU device.
+    # Weight-gradient products of nearly two rounds of 256 x 256 tiles with
+    # ragged edges and token counts (FC1: [1152, 24400] = 5 x 96 tiles, FC2: 96 x 5,
+    # over 136 tokens), which the launcher gives to the persistent kernel on a
+    # 256-CU device.
     "persist_bf16": StageConfig(
-        name="persist_bf16", layers=1, hidden=1152, heads=9, ffn=16200, seq=128, micro_batch=2,
+        name="persist_bf16", layers=1, hidden=1152, heads=9, ffn=24400, seq=136, micro_batch=1,
         causal=True, dtype="bf16", n_mb=3, rerouted=(2,), schedule="1f1b_deferred_shuffled_w",
         warmup=2, perturbed=True),
     "tiny_noncausal": CONFIGS["tiny"].with_(name="tiny_noncausal", causal=False),

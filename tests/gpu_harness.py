@@ -83,3 +83,20 @@ def run_gpu(cfg, ops=None, params=None, x_fn=None, dy_fn=None, stage=None, read_
     if own:
         stage.close()
     return out
+
+
+def takes(cfg, n=1, attention=None, **products) -> None:
+    """Asserts the kernels that cfg runs on 256 compute units (elsewhere the
+    choice differs and the test compares results alone): the attention kernels,
+    and (tile, splits) of products over the tokens of n micro-batches."""
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        return
+    from paper_2405_14009_amd import Stage
+    from tests import plans
+    if attention is not None:
+        kind = Stage.from_config(cfg, dry_run=True).attention_kernels()
+        assert kind == attention, (kind, attention)
+    if products:
+        got = plans.stage(cfg, n)
+        assert {k: got[k] for k in products} == products, got

@@ -6,7 +6,7 @@ import pytest
 import oracle
 from synth import gen_params, get_config
 from tests.conftest import rel_l2
-from tests.gpu_harness import log, run_gpu
+from tests.gpu_harness import log, run_gpu, takes
 
 pytestmark = pytest.mark.gpu
 
@@ -28,10 +28,11 @@ FORMS = {
 }
 
 
-def narrow(form, d, **kw):
+def narrow(form, d):
     f = FORMS[form]
-    return get_config("small_bf16").with_(layers=1, hidden=d * f["heads"], ffn=2 * d * f["heads"], n_mb=1, rerouted=(),
-                                          **f, **kw)
+    cfg = get_config("small_bf16").with_(layers=1, hidden=d * f["heads"], ffn=2 * d * f["heads"], n_mb=1, rerouted=(), **f)
+    takes(cfg, attention="block" if form == "bidirectional" else form)
+    return cfg
 
 
 @pytest.mark.parametrize("d", [32, 64, 96])

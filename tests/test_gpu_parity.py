@@ -18,7 +18,7 @@ import pytest
 import oracle
 from synth import CONFIGS, TEST_CONFIGS, MB, gen_dy, gen_params, gen_x, get_config, op_list
 from tests.conftest import compare_grads, rel_l2
-from tests.gpu_harness import log, run_gpu
+from tests.gpu_harness import log, run_gpu, takes
 
 pytestmark = pytest.mark.gpu
 
@@ -86,12 +86,9 @@ def check_adam_on_gpu_grads(cfg, g, params0, hp=None):
 def test_elementwise_parity(name):
     cfg = get_config(name)
     if name == "persist_bf16":
-        # FC1 / FC2 weight gradients: 320 tiles of 256 x 256 (ragged), a multiple of 8 and more
-        # than one per compute unit, so the launcher takes the persistent kernel
-        import torch
-        cus = torch.cuda.get_device_properties(0).multi_processor_count
-        tiles = -(-cfg.hidden // 256) * -(-cfg.ffn // 256)
-        assert tiles % 8 == 0 and tiles > cus, (tiles, cus)
+        takes(cfg, w_fc1=("persist", 1), w_fc2=("persist", 1))
+    if name == "wide_bf16":
+        takes(cfg, f_fc1=("256", 1), d_fc2=("256", 1), w_fc1=("256", 1), w_fc2=("256", 1))
     log(f"[parity] {name}: shapes L={cfg.layers} h={cfg.hidden} a={cfg.heads} f={cfg.ffn} "
         f"s={cfg.seq} b={cfg.micro_batch} {cfg.dtype} causal={cfg.causal}")
     g = run_gpu(cfg)
@@ -112,15 +109,17 @@ def test_elementwise_parity(name):
     dict(seq=328),                                    # ragged: last query / key blocks partial
     dict(seq=328, causal=False, micro_batch=3, n_mb=2),
     dict(seq=64, micro_batch=3, n_mb=2),              # one key block
-    dict(seq=1000, n_mb=2),                           # 8 query blocks: 4 pairs of unequal halves
-    dict(seq=136, n_mb=2),                            # 2 query blocks, the last one's key range capped at s
+    dict(seq=1000, n_mb=2),                           # 16 key blocks, four per wave at the last queries
+    dict(seq=136, n_mb=2),                            # the last key block 8 wide; waves without keys
     dict(seq=8, micro_batch=4, n_mb=2),               # the shortest sequence the stage takes
 ])
 def test_attention_variants_parity(variant):
     """bf16 stages with head dimension 128 take the fused attention path
     (scores never materialised); non-causal, ragged and multi-sequence
-    micro-batches against the oracle."""
+    micro-batches against the oracle.  These grids are small: workgroups of 32
+    queries (the paired and per-block kernels have tests of their own)."""
     cfg = get_config("small_bf16").with_(**variant)
+    takes(cfg, attention="split")
     log(f"[attn] {variant}: s={cfg.seq} b={cfg.micro_batch} causal={cfg.causal}")
     g = run_gpu(cfg)
     o = oracle.run_oplist(cfg)
@@ -203,10 +202,10 @@ def _grouped(ops):
                                       ("persist_bf16", None)])
 def test_batched_weight_pass(name, seq):
     """One weight pass over several deferred micro-batches (one product per
-    parameter over their concatenated tokens; for bf16 token counts that are
-    not a multiple of 64, one product per micro-batch) equals one call per
-    micro-batch (fp32 sums in another order: rel <= 1e-6), logs the same
-    records, and matches the oracle."""
+    parameter over their concatenated tokens; for token counts that are not a
+    multiple of a k-tile each micro-batch's last one is padded with zeros) equals
+    one call per micro-batch (fp32 sums in another order: rel <= 1e-6), logs the
+    same records, and matches the oracle."""
     cfg = get_config(name)
     if seq:
         cfg = cfg.with_(seq=seq)

@@ -6,9 +6,10 @@ against the fp64 oracle.  Bars are those of tests/test_gpu_parity.py (rel-L2
 import pytest
 
 import oracle
-from synth import get_config
+from paper_2405_14009_amd import RC_READ_GRAD, Stage
+from synth import MB, gen_params, get_config
 from tests.conftest import compare_grads, rel_l2
-from tests.gpu_harness import log, run_gpu
+from tests.gpu_harness import log, run_gpu, takes
 
 pytestmark = pytest.mark.gpu
 
@@ -43,6 +44,7 @@ def test_attention_head_widths(d, seq, causal):
     the shortest sequences."""
     cfg = get_config("small_bf16").with_(layers=1, hidden=4 * d, heads=4, ffn=16 * d, seq=seq, n_mb=2,
                                          rerouted=(1,), causal=causal)
+    takes(cfg, attention="materialised" if seq == 128 else "split")
     check(cfg, 2e-2)
 
 
@@ -50,36 +52,33 @@ def test_attention_head_widths(d, seq, causal):
 def test_attention_head_widths_per_block(d):
     """The per-query-block causal kernels of narrow heads (160 pairs of query
     blocks fill 256 compute units poorly)."""
-    from paper_2405_14009_amd import Stage
     cfg = get_config("block_bf16").with_(hidden=10 * d, ffn=20 * d, seq=1000, n_mb=1, rerouted=())
-    stage = Stage.from_config(cfg, dry_run=True)
-    assert stage.attention_kernels() == "block"
+    takes(cfg, attention="block")
     check(cfg, 2e-2)
 
 
-@pytest.mark.parametrize("d", [32, 64, 80, 120])
-def test_attention_head_widths_paired(d):
-    """Narrow heads on a grid whose pairs of query blocks fill 256 compute units once."""
-    from paper_2405_14009_amd import Stage
-    cfg = get_config("small_bf16").with_(layers=1, hidden=16 * d, heads=16, ffn=8 * d, seq=1000, micro_batch=4, n_mb=1,
-                                         rerouted=())
-    import torch
-    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        assert Stage.from_config(cfg, dry_run=True).attention_kernels() == "paired"
+@pytest.mark.parametrize("d", [32, 64, 80, 120, 128])
+@pytest.mark.parametrize("seq,micro_batch", [(1000, 4), (328, 8)])
+def test_attention_head_widths_paired(d, seq, micro_batch):
+    """Grids whose pairs of query blocks fill 256 compute units once: eight ragged
+    query blocks, and three, whose middle one pairs with itself."""
+    cfg = get_config("small_bf16").with_(layers=1, hidden=16 * d, heads=16, ffn=8 * d, seq=seq, micro_batch=micro_batch,
+                                         n_mb=1, rerouted=())
+    takes(cfg, attention="paired")
     check(cfg, 2e-2)
 
 
-@pytest.mark.parametrize("d", [32, 64, 80, 120])
+@pytest.mark.parametrize("d", [32, 64, 80, 120, 128])
 def test_attention_head_widths_blocks_noncausal(d):
-    """Narrow bidirectional heads on a grid of more 32-row workgroups than compute units hold."""
+    """Bidirectional heads on a grid of more 32-row workgroups than compute units hold."""
     cfg = get_config("small_bf16").with_(layers=1, hidden=4 * d, heads=4, ffn=8 * d, seq=1128, micro_batch=4, n_mb=1,
                                          rerouted=(), causal=False)
+    takes(cfg, attention="block")
     check(cfg, 2e-2)
 
 
 # Token counts and widths one chunk of 8 to either side of 64, 128 and 256, a
-# single k-tile and long reductions; several micro-batches whose token counts
-# are no multiple of a k-tile.
+# single k-tile and long reductions.
 SHAPES = [dict(hidden=64, heads=1, ffn=64, seq=64, micro_batch=1, n_mb=1),
           dict(hidden=56, heads=1, ffn=72, seq=8, micro_batch=1, n_mb=2),
           dict(hidden=136, heads=1, ffn=264, seq=72, micro_batch=1, n_mb=3),
@@ -99,8 +98,52 @@ def test_192_row_tiles():
     """FC1 forward and FC2 input gradient of [1800, 5032] over 768 fill 256
     compute units best in 192x256 tiles, ragged in both directions and in a
     tile count that is no multiple of the XCDs."""
-    check(get_config("small_bf16").with_(layers=1, hidden=768, heads=6, ffn=5032, seq=600, micro_batch=3, n_mb=1,
-                                         rerouted=()), 2e-2)
+    cfg = get_config("small_bf16").with_(layers=1, hidden=768, heads=6, ffn=5032, seq=600, micro_batch=3, n_mb=1,
+                                         rerouted=())
+    takes(cfg, f_fc1=("192x256", 1), d_fc2=("192x256", 1))
+    check(cfg, 2e-2)
+
+
+# One weight pass over several micro-batches whose token counts are no multiple
+# of a k-tile: every tile of the weight-gradient layout, unsplit and with splits
+# that end inside a segment; the persistent kernel over few and many k-tiles.
+SEGMENTED = [
+    (3, dict(hidden=64, heads=1, ffn=128, seq=72, micro_batch=1), dict(w_qkv=("32", 1), w_o=("32", 1), w_fc1=("32", 1))),
+    (3, dict(hidden=264, heads=3, ffn=1032, seq=1000, micro_batch=3), dict(w_qkv=("64", 7), w_o=("64", 10))),
+    (3, dict(hidden=768, heads=6, ffn=3080, seq=328, micro_batch=2), dict(w_qkv=("64", 1), w_fc1=("128", 3))),
+    (3, dict(hidden=1152, heads=9, ffn=5128, seq=328, micro_batch=2), dict(w_qkv=("128", 1), w_fc1=("128", 1))),
+    (3, dict(hidden=1280, heads=10, ffn=5128, seq=1000, micro_batch=1), dict(w_fc1=("256x128", 1))),
+    (3, dict(hidden=1280, heads=10, ffn=5128, seq=1000, micro_batch=3),
+     dict(w_qkv=("256", 3), w_o=("256x128", 5), w_fc1=("256", 2), w_fc2=("256", 2))),
+    (2, dict(hidden=1152, heads=9, ffn=8008, seq=600, micro_batch=3), dict(w_fc1=("256", 1), w_fc2=("256", 1))),
+    (3, dict(hidden=1152, heads=9, ffn=24400, seq=136, micro_batch=1), dict(w_fc1=("persist", 1), w_fc2=("persist", 1))),
+    (3, dict(hidden=1152, heads=9, ffn=24400, seq=1000, micro_batch=3), dict(w_fc1=("persist", 1), w_fc2=("persist", 1))),
+]
+
+
+@pytest.mark.parametrize("n,shape,want", SEGMENTED)
+def test_segmented_weight_products(n, shape, want):
+    """The batched pass against one call per micro-batch (fp32 sums in another
+    order: rel <= 1e-6) and against the oracle."""
+    from synth.schedules import Op
+    cfg = get_config("small_bf16").with_(layers=1, n_mb=n, rerouted=(), **shape)
+    assert cfg.tokens % 64
+    takes(cfg, n, **want)
+    log(f"[segments] n={n} {shape} {want}")
+    mbs = [MB(j, 0) for j in range(n)]
+    ops = [Op(k, m) for k in ("F", "B") for m in mbs]
+    got = {}
+    for name, ws in (("one", [Op("W", m) for m in mbs]), ("batch", [Op("W*", mbs)])):
+        stage = Stage.from_config(cfg)
+        params = gen_params(cfg)
+        stage.load_params(params)
+        run_gpu(cfg, ops + ws, stage=stage, read_state=False, keep_outputs=False)
+        got[name] = stage.read_all(RC_READ_GRAD)
+        stage.close()
+    for p in range(12):
+        assert rel_l2(got["batch"][0][p], got["one"][0][p]) < 1e-6, p
+    o = oracle.run_oplist(cfg, ops + [Op("W", m) for m in mbs], params=params)
+    log(f"[segments] worst gradient rel-L2 {compare_grads(cfg, got['batch'], o.grads, 2e-2):.2e}")
 
 
 def test_split_products_are_reproducible():
@@ -120,8 +163,6 @@ def test_f32_rows_beyond_buffer_offsets():
     tile's 64 token rows starts 2^31 bytes past its first.  The FFN's weights are
     zero but for 64 columns spread over it, where gelu(0) = 0 leaves the same
     stage as one of 64 FFN columns, which the oracle runs."""
-    from paper_2405_14009_amd import RC_READ_GRAD, Stage
-    from synth import MB, gen_params
     from synth.schedules import Op
     import numpy as np
     f = 8600000
