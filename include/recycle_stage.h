@@ -68,8 +68,8 @@ typedef enum rc_dtype {
  *  - bf16 stages: every matrix the matrix-core kernels read through a
  *    buffer descriptor fits its 2^31 - 1 byte range: 2 T max(3 hidden, ffn)
  *    (activation operands, T = micro_batch * seq_len), 2 hidden
- *    max(3 hidden, ffn) (weights) and, without fused attention, 2 seq_len^2
- *    (one head's probabilities).
+ *    max(3 hidden, ffn) (weights) and, for head_dim != 128, 2 seq_len^2 (one
+ *    head's probabilities, also where the fused attention keeps none).
  * causal = 1 masks keys after the query (GPT). */
 typedef struct rc_stage_config {
   int32_t num_layers;

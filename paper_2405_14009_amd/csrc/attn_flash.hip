@@ -62,6 +62,12 @@ bool args_ok(int heads, int h) {
 
 }  // namespace
 
+// Narrow heads keep the materialised kernels for sequences of one query block.
+// They are slower there too (us, one layer, materialised / fused, 16 heads: of 32,
+// 64 sequences of 64, 419 / 312; of 64, 8 of 128, 290 / 254; of 96, one of 32,
+// 189 / 180), but the fused kernels keep 2 d + 8 bytes per row and head where the
+// probabilities take 2 s, so below s = d + 4 a stage would hold more from F to
+// B_input than its stash account counts.
 bool attn_flash_supported(int elt, int head_dim, int s) {
   if (elt != 2 || head_dim > 128 || head_dim % 8) return false;
   return head_dim == 128 || s > 128;

@@ -68,9 +68,7 @@ hipError_t softmax_backward(int elt, const float* dP, const void* P, void* dS, l
 // floats.  h == heads * d.  orest [b*s, h] (written by the forward, read by the
 // backward; narrow heads only): what the bf16 rounding
 // of o drops.  Head dimensions other than 128 take it for
-// sequences of more than one query block (128); up to that the materialised
-// kernels stay, whose probabilities are small there, as stages of short
-// sequences and narrow heads report through rc_stage_attention_kernels.
+// sequences of more than one query block (128).
 bool attn_flash_supported(int elt, int head_dim, int s);
 // The kernels that fused attention over b sequences of s tokens and `heads`
 // heads runs on the current device: one workgroup per query block, per pair of
