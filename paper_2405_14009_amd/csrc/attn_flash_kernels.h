@@ -1084,7 +1084,8 @@ static __device__ __forceinline__ void attn_bwd_q_pair(const AttnArgs& p) {
 // queries (or keys), and its four waves walk every fourth block of the other
 // side each, with tiles of their own: no barrier until the four partial states
 // are combined through LDS in wave order.  At that shape: forward 14.6 -> 7.2,
-// dQ 18.3 -> 8.4, dK/dV 14.7 -> 8.0 us.
+// dQ 18.3 -> 8.4, dK/dV 14.7 -> 8.0 us (7.6, 9.0 and 8.4 since narrow heads keep
+// two row statistics and the rest of O).
 static constexpr int SPLIT_TILE = 2 * TILE64 + VECS;  // a wave's two tiles (and row vectors)
 
 // This wave's copies have landed; its LDS reads stay behind (no other wave
